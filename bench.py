@@ -92,19 +92,22 @@ def roofline(tm, n, esz, launches_ms, launches, counter_file=None, tune=None):
     # the per-entry operator count (3 state words + stiffness row with one value per
     # entry + two diagonal coefficients, over B), for comparison
     entry_bytes = step_kernel_bytes(n, nnz_off, B, esz) + esz * n
-    return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+    per_entry_s = avg_launch_s / max(1, tm["steps_per_launch"])
+    return {"bound": "hbm" if tm["steps_per_launch"] <= 1 else "valu", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
             "traffic": (traffic_from_profile(counter_file, B, tm["variant"])
-                        if counter_file else None),
-            "kernel": f"k_step (B={B}, {'FP32' if esz == 4 else 'FP64'}, variant {tm['variant']})",
+                        if counter_file and tm["steps_per_launch"] <= 1 else None),
+            "kernel": (f"{tm['steps_per_launch']} steps per launch (B={B}, {'FP32' if esz == 4 else 'FP64'})"
+                       if tm["steps_per_launch"] > 1 else
+                       f"k_step (B={B}, {'FP32' if esz == 4 else 'FP64'}, variant {tm['variant']})"),
             "bytes_per_launch": launch_bytes, "avg_launch_us": avg_launch_s * 1e6,
             "avg_launch_timing": ("HIP events on the library's stream around the replayed "
                                   "step graphs (and around each direct launch): kernel time "
                                   "plus the gaps between graph nodes, so at or above the "
                                   "profiler's kernel average"),
             "per_entry_bytes_per_launch": entry_bytes,
-            "per_entry_frac": entry_bytes / avg_launch_s / 1e9 / HBM_PEAK_GBS,
-            "bytes_per_node_update": launch_bytes / (n * B),
+            "per_entry_frac": entry_bytes / per_entry_s / 1e9 / HBM_PEAK_GBS,
+            "bytes_per_node_update": launch_bytes / (n * B) / max(1, tm["steps_per_launch"]),
             "launch_variant_tuning_us": tune}
 
 

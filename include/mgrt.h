@@ -66,9 +66,8 @@ extern "C" {
 #define MGRT_F_JAC_PAIRED 256  /* MG Jacobian: keep one source run and one receiver run */
                                /* per pair even when every receiver coincides with its  */
                                /* source (default there: one run, see jacobian_coarse)  */
-#define MGRT_F_ONE_STEP 512    /* one launch per leap-frog step also where a small mesh  */
-                               /* would take several steps per launch (one-column     */
-                               /* forward runs on meshes of at most 256 tiles)          */
+#define MGRT_F_ONE_STEP 512    /* one launch per leap-frog step also where a run would   */
+                               /* take several steps per launch (mgrt_forward_traces)   */
 
 /* stepping variants */
 #define MGRT_STEP_BATCHED 0    /* multi-source node-major ELL launch (default)           */
@@ -111,7 +110,8 @@ typedef struct {
     int variant;               /* launch variant of the last stepping run (0..15, as in */
                                /* mgrt_run_opts.launch - 1)                              */
     double step_bytes;         /* algorithmic HBM bytes of those launches: per node and  */
-                               /* column 3 state words (+1 velocity out, +1 velocity in */
+                               /* column 3 state words (4 for a launch of several steps; */
+                               /* per step +1 velocity out, +1 velocity in              */
                                /* in adjoint sweeps); per node beta, the stiffness row's */
                                /* column ids, its coefficients (one where all are equal) */
                                /* and (adjoint) the FP64 accumulator                     */
@@ -133,7 +133,7 @@ typedef struct {
                                /* otherwise                                             */
     int steps_per_launch;      /* leap-frog steps per stepping launch of the last run:  */
                                /* 1, or k when each workgroup advanced its tile and the */
-                               /* tile's k-ring k steps in LDS (small one-column runs)  */
+                               /* tile's k-ring (or each wave its strip) k steps        */
 } mgrt_timing;
 
 /* Create a context on HIP device `device`.  `hip_stream` is a hipStream_t to launch
@@ -189,11 +189,14 @@ int mgrt_stability_bound(mgrt_ctx *ctx, double *dt_max);
  * MGRT_E_ARG if n_src, n_rec or n_steps is below 1, a pointer is NULL or a point lies
  * outside the mesh; MGRT_E_UNSTABLE if dt exceeds mgrt_stability_bound (unless
  * MGRT_F_SKIP_STABILITY), MGRT_E_NONFINITE if a coordinate, a wavelet sample or a trace
- * is not finite.  Runs of one source without a PML on meshes of at most 256 tiles
- * (65,536 nodes) whose tiles' k-rings fit in LDS for some k >= 2 advance k steps per
- * launch, each workgroup stepping its tile and the tile's k-ring in the stiffness graph
- * (the same node updates; MGRT_F_ONE_STEP keeps one launch per step;
- * mgrt_timing.steps_per_launch reports which ran). */
+ * is not finite.  Runs without a PML take k steps per launch where that is faster: each
+ * workgroup steps a compact tile and the tile's k-ring in the stiffness graph in LDS, or each
+ * wave a strip of a lexicographic 2D grid (the same node updates; a run of several columns
+ * gives the one-step launches' values bit for bit, a one-column run on up to 65,536 nodes
+ * agrees with them to rounding).  One launch per step stays for runs of several columns below
+ * 256 steps, a requested launch variant or batch width above 1, 3D meshes beyond some 100,000
+ * words of state, tiles with more than 64 loads or taps of a column group, and
+ * MGRT_F_ONE_STEP (mgrt_timing.steps_per_launch reports which ran). */
 int mgrt_forward_traces(mgrt_ctx *ctx, int64_t n_src, const double *src_xyz, int32_t n_rec,
                         const double *rec_xyz, const double *wavelet, double dt,
                         int64_t n_steps, const mgrt_run_opts *opts, double *traces);

@@ -159,8 +159,8 @@ class Context:
                        graph=True, one_step=False):
         """launch: 0 = the tuned launch variant, 1..16 = variant launch - 1.  graph=False
         launches every step directly (MGRT_F_NO_GRAPH) instead of replaying captured runs
-        of steps.  one_step=True (MGRT_F_ONE_STEP) keeps one launch per step where a small
-        one-column run would take several steps per launch."""
+        of steps.  one_step=True (MGRT_F_ONE_STEP) keeps one launch per step where a run
+        would take several steps per launch."""
         src, rec = self._acq(src, rec)
         wav = _arr(wavelet, np.float64)
         if wav.shape[0] < n_steps:

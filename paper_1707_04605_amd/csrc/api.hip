@@ -107,6 +107,7 @@ static std::vector<double> forward_impl(Ctx &c, const Acquisition &aq, const dou
         const int B = pick_batch(c, prec, aq.n_src, opts ? opts->batch : 0, dt, flags);
         const int S = tile_nodes(prec, B);
         StepOp &op = get_step_op(c, S, prec, dt);
+        const Blocks *blocks = plan_blocks(c, prec, op, std::min<int64_t>(B, aq.n_src), B, n_steps, opts);
         const size_t esz = prec == 32 ? 4 : 8;
         DevBuf series = upload(g, c.stream);
         DevBuf bufA(n * B * esz), bufB(n * B * esz);
@@ -138,6 +139,7 @@ static std::vector<double> forward_impl(Ctx &c, const Acquisition &aq, const dou
             MGRT_HIP(hipMemsetAsync(bufB.p, 0, bufB.bytes, c.stream));
             run.d_p = bufA.p;
             run.d_pm = bufB.p;
+            run.blocks = blocks;
             run_batch(c, op, run);
             MGRT_HIP(hipMemcpy(hp.data(), parts.p, hp.size() * sizeof(double), hipMemcpyDeviceToHost));
             for (int b = 0; b < nb; ++b)
@@ -370,6 +372,8 @@ int mgrt_upload_mesh(mgrt_ctx *ctx, int dim, int64_t n_nodes, const double *coor
         c.ops.clear();
         c.tuned.clear();
         c.batch_tuned.clear();
+        c.blocks.clear();
+        c.grid_nx = -1;
         build_host_mesh(c.hm, dim, n_nodes, coords, n_elems, elems, n_bfacets, bfacets, admittance,
                         n_coarse, coarse_of_elem, coarse_verts);
         HostMesh &hm = c.hm;

@@ -123,6 +123,7 @@ void gradient_t(Ctx &c, const Acquisition &aq, const std::vector<double> &g, dou
             fr.inj = fwd_inj;
             fr.d_p = cur; fr.d_pm = prev;
             fr.d_q = qsz ? fq.p : nullptr;
+            if (B == 1) fr.blocks = plan_blocks(c, prec, op, 1, 1, a1 - a0, opts);
             run_batch(c, op, fr);
             cur = fr.d_p; prev = fr.d_pm;
         }

@@ -326,6 +326,9 @@ void jacobian_mg(Ctx &c, const Acquisition &aq, const std::vector<double> &g,
     std::vector<int64_t> hist_nodes(hm.cnodes.begin(), hm.cnodes.end());
 
     StepOp &opf = get_step_op(c, tile_nodes(prec, Bf), prec, dt);
+    // several steps per launch where their second pair of state buffers also fits the plan
+    const bool room = need(Bf, Bi) + (nsets == 2 ? set_bytes : 0) + (size_t)n * esz * 2 * std::max(Bf, Bi) <= cap;
+    const Blocks *blocks = room ? plan_blocks(c, prec, opf, std::min<int64_t>(Bf, aq.n_src), Bf, N, opts) : nullptr;
     MGRT_HIP(hipFuncSetAttribute((const void *)k_corr<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     if (mono) {
         // One run per source batch with w1 at the source points: the field to lh, the
@@ -358,6 +361,7 @@ void jacobian_mg(Ctx &c, const Acquisition &aq, const std::vector<double> &g,
             MGRT_HIP(hipMemsetAsync(stA.p, 0, (size_t)n * Bf * esz, c.stream));
             MGRT_HIP(hipMemsetAsync(stB.p, 0, (size_t)n * Bf * esz, c.stream));
             mr.d_p = stA.p; mr.d_pm = stB.p;
+            mr.blocks = blocks;
             run_batch(c, opf, mr);
             MGRT_HIP(hipEventRecord(side.ev[2], c.stream));
             MGRT_HIP(hipStreamWaitEvent(side.s, side.ev[2], 0));
@@ -386,11 +390,13 @@ void jacobian_mg(Ctx &c, const Acquisition &aq, const std::vector<double> &g,
         MGRT_HIP(hipMemsetAsync(stA.p, 0, (size_t)n * Bf * esz, c.stream));
         MGRT_HIP(hipMemsetAsync(stB.p, 0, (size_t)n * Bf * esz, c.stream));
         fr.d_p = stA.p; fr.d_pm = stB.p;
+        fr.blocks = blocks;
         run_batch(c, opf, fr);
 
         // impulse runs from the receivers of this source batch
         const int64_t P = (int64_t)nb * aq.n_rec;
         StepOp &opi = get_step_op(c, tile_nodes(prec, Bi), prec, dt);
+        const Blocks *iblocks = room ? plan_blocks(c, prec, opi, std::min<int64_t>(Bi, P), Bi, N, opts) : nullptr;
         for (int64_t q0 = 0; q0 < P; q0 += Bi) {
             const int nq = (int)std::min<int64_t>(Bi, P - q0);
             BatchRun ir;
@@ -412,6 +418,7 @@ void jacobian_mg(Ctx &c, const Acquisition &aq, const std::vector<double> &g,
             MGRT_HIP(hipMemsetAsync(stA.p, 0, (size_t)n * Bi * esz, c.stream));
             MGRT_HIP(hipMemsetAsync(stB.p, 0, (size_t)n * Bi * esz, c.stream));
             ir.d_p = stA.p; ir.d_pm = stB.p;
+            ir.blocks = iblocks;
             run_batch(c, opi, ir);
             if (deconv) deconvolve_series(c, lh.p, prec, nc_nodes * Bi, N, wav, delta, dscratch);
             DevBuf dfcol = upload(fcol, c.stream), dpair = upload(pair, c.stream);
@@ -541,6 +548,7 @@ void jacobian_exact(Ctx &c, const Acquisition &aq, const std::vector<double> &g,
             MGRT_HIP(hipMemsetAsync(stA.p, 0, (size_t)n * Bt * esz, c.stream));
             MGRT_HIP(hipMemsetAsync(stB.p, 0, (size_t)n * Bt * esz, c.stream));
             tr.d_p = stA.p; tr.d_pm = stB.p;
+            if (Bt == 1) tr.blocks = plan_blocks(c, prec, opt, 1, 1, N, opts);
             run_batch(c, opt, tr);
             MGRT_HIP(hipMemcpy(hp.data(), parts.p, hp.size() * 8, hipMemcpyDeviceToHost));
             for (int q = 0; q < nt; ++q) {

@@ -196,11 +196,12 @@ struct StepOp {
     // dominant neighbour-offset pattern of the records (speculative-gather launches)
     bool spec_ok = false;
     int32_t spec_off[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    DevBuf strip_coef;         // T, [n][4]: the coefficients by neighbour of a lexicographic 2D grid
+                               // (strips.hpp), filled on first use after the values change
+    DevBuf strip_rows;         // int32 per grid row: 1 where a node has no lower neighbour
+    uint64_t version = 0, strip_coef_version = 0;
     std::vector<double> gamma; // host, n (injection weights)
     PmlOp pml;
-    // several-steps-per-launch tables for small meshes (multistep.hip), built on first use
-    // and dropped whenever the values are refilled
-    std::shared_ptr<void> multi;
 };
 
 // Launch-variant timing of one stepping configuration (best of two rounds per variant on
@@ -210,6 +211,8 @@ struct Tuned {
     double us[16] = {};
     double best_us = 0;
 };
+
+struct Blocks;             // multistep.hip: tiles and regions of several-steps launches
 
 struct Ctx {
     int device = 0;
@@ -231,6 +234,9 @@ struct Ctx {
     std::map<std::tuple<int, int>, std::unique_ptr<StepOp>> ops;   // key (S, prec)
     std::map<std::tuple<int, int, int, int>, Tuned> tuned;         // (prec, B, S, W) -> variant
     std::map<std::tuple<int, int64_t>, int> batch_tuned;           // (prec, columns) -> B
+    // (bytes per entry and field, tiles asked for, steps) -> regions; dropped with the mesh
+    std::map<std::tuple<int, int64_t, int>, std::shared_ptr<Blocks>> blocks;
+    int64_t grid_nx = -1;              // row length of a lexicographic 2D grid, 0: none, -1: not looked at
     std::shared_ptr<void> fft_plans;   // deconv.hip: FFT plans kept per (length, batch, precision)
     mgrt_timing timing{};
 };
@@ -302,11 +308,26 @@ struct BatchRun {
     // allocation-free runs: every device buffer of the run comes from this arena, the steps
     // are launched directly (no graph, no tuning, no per-launch events)
     Arena *arena = nullptr;
+    // several steps per launch on these regions (plan_blocks); null: one launch per step
+    const Blocks *blocks = nullptr;
+    void *d_alt_p = nullptr, *d_alt_pm = nullptr;   // their second buffer pair (null: allocated
+                                                    // by the run, which without room for it
+                                                    // takes one launch per step)
 };
 int64_t pml_entries(const Ctx &c);
-// multistep.hip: several steps per launch where the run and mesh allow it (false: the
-// caller steps one launch per step)
-bool run_multistep(Ctx &c, StepOp &op, BatchRun &run);
+// multistep.hip: the regions for runs of n_cols columns at batch width B in a call of
+// n_steps steps (null: one launch per step).  The state, velocity and PML layout of a run
+// differs between the two, so runs that hand a state on all take one or the other.
+Blocks *plan_blocks(Ctx &c, int prec, const StepOp &op, int64_t n_cols, int B, int64_t n_steps,
+                    const mgrt_run_opts *opts, bool corr = false);
+// whether the loads and taps of run fit the regions' lists
+bool blocks_hold(const Ctx &c, const Blocks &B, const BatchRun &run);
+// false: the lists do not fit (nothing ran)
+bool run_blocks(Ctx &c, StepOp &op, BatchRun &run);
+// step.hip: move a chunk of count staged history steps, the last of the *done steps so
+// far, to the time-contiguous series of run
+void hist_flush(const BatchRun &run, int prec, const void *stage, const void *stage2, int64_t nser, int64_t count,
+                const int64_t *done, hipStream_t s);
 
 // deconv.hip: in-place Tikhonov deconvolution of n_series contiguous series of length N
 // (FP32 or FP64) by the source function f (N samples), relative regularisation delta,

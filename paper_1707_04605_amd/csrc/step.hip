@@ -32,7 +32,7 @@
 // The kernels and their launch mapping are in step_kernels.hpp.  This file is the host
 // side: the operator in SELL slices and packed records, the tile lists of loads, taps and
 // histories, the launch variants and batch widths and their tuning, and runs of steps
-// captured and replayed as graphs; small one-column runs go to multistep.hip first.
+// captured and replayed as graphs.  Runs of several steps per launch are in multistep.hip.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -108,6 +108,7 @@ static void fill_values(Ctx &c, StepOp &op) {
         }
     }, 64);
     op.beta = upload(beta, c.stream);
+    op.version++;
     op.vals = upload(vals, c.stream);
     // packed per-node records for the packed launches: beta, the coefficient shared by all
     // W entries (0 when they differ: then the first column id carries REC_GENERAL and the
@@ -294,7 +295,6 @@ StepOp &get_step_op(Ctx &c, int S, int prec, double dt) {
     if (op.dt != dt || op.eps_version != c.eps_version) {
         op.dt = dt;
         op.eps_version = c.eps_version;
-        op.multi.reset();
         if (prec == 32) fill_values<float>(c, op);
         else fill_values<double>(c, op);
     }
@@ -490,7 +490,6 @@ void run_batch_t(Ctx &c, StepOp &op, BatchRun &run) {
     const int64_t n = c.hm.n;
     hipStream_t s = c.stream;
     MGRT_REQUIRE(tile_nodes(op.prec, run.B) == S, MGRT_E_ARG, "batch width does not match operator tiles");
-    if (run_multistep(c, op, run)) return;
     c.timing.steps_per_launch = 1;
     const std::vector<int32_t> &ip = c.hm.iperm;
     TileLists inj = make_lists(run.inj, S, op.n_tiles, ip, [](const Injection &e) { return e.sid; },
@@ -815,7 +814,27 @@ int64_t pml_entries(const Ctx &c) {
     return ne;
 }
 
+void hist_flush(const BatchRun &run, int prec, const void *stage, const void *stage2, int64_t nser, int64_t count,
+                const int64_t *done, hipStream_t s) {
+    auto go = [&](auto zero, const void *st, void *hist) {
+        typedef decltype(zero) T;
+        hipLaunchKernelGGL(k_hist_flush<T>, dim3((nser + 63) / 64), dim3(256), 0, s, static_cast<const T *>(st),
+                           nser, (int)count, static_cast<T *>(hist), run.hist_len, run.hist_off - count,
+                           (int)run.reverse_hist, done);
+    };
+    for (int q = 0; q < (run.hist_mode == 2 ? 2 : 1); ++q) {
+        const void *st = q ? stage2 : stage;
+        void *hist = q ? run.d_hist2 : run.d_hist;
+        if (prec == 32) go(0.0f, st, hist);
+        else go(0.0, st, hist);
+    }
+}
+
 void run_batch(Ctx &c, StepOp &op, BatchRun &run) {
+    if (run.blocks) {
+        if (run_blocks(c, op, run)) return;
+        MGRT_REQUIRE(!run.d_alt_p, MGRT_E_STATE, "a run's loads or taps do not fit its regions");
+    }
     if (op.prec == 32) run_batch_t<float>(c, op, run);
     else run_batch_t<double>(c, op, run);
 }
