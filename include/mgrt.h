@@ -25,6 +25,8 @@
  *   - Array arguments are host pointers owned by the caller unless the argument
  *     says "device" or opts->flags has MGRT_F_DEVICE_OUT for outputs.  The library
  *     copies what it keeps into device memory it owns and frees in mgrt_destroy().
+ *     Device blocks that a call frees wait for later calls of any context, up to 16 GiB
+ *     per device, until the device's last context is destroyed.
  *   - Calls are synchronous with respect to the host: on return, outputs are written.
  *   - A context is not thread-safe; separate contexts are independent.
  *   - All floating-point inputs are FP64; "precision" selects the arithmetic of the

@@ -9,6 +9,105 @@
 
 namespace mgrt {
 
+// ------------------------------------------------------------------------------------
+// Device blocks between calls.  Bounded (CACHE_BYTES per device), shared by all contexts of
+// a device under a mutex, drained when an allocation fails and when the device's last
+// context is destroyed.  A block enters only after the device is idle, as hipFree would
+// wait, so that no kernel of another stream still uses it.
+namespace {
+
+constexpr size_t CACHE_MIN = 1 << 20;             // smaller blocks: hipMalloc takes about 1 us
+constexpr int CACHE_DEVICES = 64;
+
+struct BlockCache {
+    std::mutex mu;
+    std::vector<std::pair<size_t, void *>> blocks;   // oldest first
+    size_t bytes = 0;
+    int contexts = 0;
+};
+
+// never destroyed: contexts may outlive static objects, the runtime may not
+BlockCache *block_cache() {
+    static BlockCache *all = new BlockCache[CACHE_DEVICES];
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= CACHE_DEVICES) return nullptr;
+    return all + dev;
+}
+
+}  // namespace
+
+void *cache_take(size_t bytes, size_t *got) {
+    BlockCache *c = bytes >= CACHE_MIN ? block_cache() : nullptr;
+    if (!c) return nullptr;
+    std::lock_guard<std::mutex> lk(c->mu);
+    size_t best = c->blocks.size();
+    for (size_t i = 0; i < c->blocks.size(); ++i)
+        if (c->blocks[i].first >= bytes && c->blocks[i].first <= bytes + bytes / 8 &&
+            (best == c->blocks.size() || c->blocks[i].first < c->blocks[best].first))
+            best = i;
+    if (best == c->blocks.size()) return nullptr;
+    void *p = c->blocks[best].second;
+    *got = c->blocks[best].first;
+    c->bytes -= *got;
+    c->blocks.erase(c->blocks.begin() + best);
+    return p;
+}
+
+bool cache_give(void *p, size_t bytes, int device) {
+    int cur = -1;
+    if (bytes < CACHE_MIN || bytes > CACHE_BYTES || hipGetDevice(&cur) != hipSuccess || cur != device) return false;
+    BlockCache *c = block_cache();
+    if (!c || hipDeviceSynchronize() != hipSuccess) return false;
+    std::vector<void *> out;
+    {
+        std::lock_guard<std::mutex> lk(c->mu);
+        if (c->contexts == 0) return false;
+        size_t k = 0;
+        while (c->bytes + bytes > CACHE_BYTES) {      // the oldest make room
+            c->bytes -= c->blocks[k].first;
+            out.push_back(c->blocks[k++].second);
+        }
+        c->blocks.erase(c->blocks.begin(), c->blocks.begin() + k);
+        c->blocks.emplace_back(bytes, p);
+        c->bytes += bytes;
+    }
+    for (void *q : out) (void)hipFree(q);
+    return true;
+}
+
+bool cache_drain() {
+    BlockCache *c = block_cache();
+    if (!c) return false;
+    std::vector<std::pair<size_t, void *>> out;
+    {
+        std::lock_guard<std::mutex> lk(c->mu);
+        out.swap(c->blocks);
+        c->bytes = 0;
+    }
+    for (auto &b : out) (void)hipFree(b.second);
+    return !out.empty();
+}
+
+size_t cache_bytes() {
+    BlockCache *c = block_cache();
+    if (!c) return 0;
+    std::lock_guard<std::mutex> lk(c->mu);
+    return c->bytes;
+}
+
+// A context enters (+1) or leaves (-1) the current device; the last one drains the cache.
+static void cache_contexts(int add) {
+    BlockCache *c = block_cache();
+    if (!c) return;
+    bool last = false;
+    {
+        std::lock_guard<std::mutex> lk(c->mu);
+        c->contexts += add;
+        last = c->contexts == 0;
+    }
+    if (last) (void)cache_drain();
+}
+
 int run_precision(const mgrt_run_opts *o) {
     int p = o ? o->precision : 0;
     if (p == 0) p = 32;
@@ -332,6 +431,7 @@ int mgrt_create(int device, void *hip_stream, mgrt_ctx **out) {
         }
         ctx->c.own_stream = true;
     }
+    cache_contexts(1);
     *out = ctx;
     return MGRT_OK;
 }
@@ -343,6 +443,7 @@ int mgrt_destroy(mgrt_ctx *ctx) {
     bool own = ctx->c.own_stream;
     hipStream_t s = ctx->c.stream;
     delete ctx;
+    cache_contexts(-1);
     if (own) (void)hipStreamDestroy(s);
     return MGRT_OK;
 }

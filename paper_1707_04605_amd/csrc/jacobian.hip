@@ -169,7 +169,7 @@ __global__ void k_diff_series(const T *__restrict__ hist, int64_t E, int64_t N, 
 
 size_t free_bytes(const mgrt_run_opts *o) {
     size_t fr = 0, tot = 0;
-    MGRT_HIP(hipMemGetInfo(&fr, &tot));
+    device_memory(&fr, &tot);
     size_t cap = fr > (size_t)(2ull << 30) ? fr - (size_t)(2ull << 30) : fr / 2;   // keep 2 GiB
     if (o && o->mem_budget_gb > 0) cap = std::min(cap, (size_t)(o->mem_budget_gb * (1ull << 30)));
     return cap;

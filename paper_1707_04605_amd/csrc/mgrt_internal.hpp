@@ -36,35 +36,71 @@ struct Error : std::runtime_error {
         if (!(cond)) throw ::mgrt::Error((code), (msg));                                  \
     } while (0)
 
+// Freed blocks of 1 MiB and more wait in a per-device cache (api.hip) for the next
+// allocation of about their size: once a process has allocated and freed about the device's
+// memory, the driver wipes what is freed, and hipFree takes 30 ms per GB (4.5 GB: 0.7 ms
+// before, 135 ms after).  cache_take returns a block of at least `bytes`, or null; cache_give
+// takes a block of `device` or declines it; cache_drain frees what waits on the current device (and says
+// whether anything did); cache_bytes is how much that is.
+void *cache_take(size_t bytes, size_t *got);
+bool cache_give(void *p, size_t bytes, int device);
+bool cache_drain();
+size_t cache_bytes();
+constexpr size_t CACHE_BYTES = 16ull << 30;      // per device
+
+// Free and total bytes of the current device; cached blocks count as free.
+inline void device_memory(size_t *fr, size_t *tot) {
+    const hipError_t e = hipMemGetInfo(fr, tot);
+    if (e != hipSuccess) throw Error(MGRT_E_HIP, std::string("hipMemGetInfo: ") + hipGetErrorString(e));
+    *fr += cache_bytes();
+}
+
 // Owning device allocation.
 struct DevBuf {
     void *p = nullptr;
-    size_t bytes = 0;
+    size_t bytes = 0;          // as asked for
+    size_t held = 0;           // of the block
+    int device = -1;
     DevBuf() = default;
     explicit DevBuf(size_t b) { alloc(b); }
     DevBuf(const DevBuf &) = delete;
     DevBuf &operator=(const DevBuf &) = delete;
-    DevBuf(DevBuf &&o) noexcept : p(o.p), bytes(o.bytes) { o.p = nullptr; o.bytes = 0; }
+    DevBuf(DevBuf &&o) noexcept : p(o.p), bytes(o.bytes), held(o.held), device(o.device) {
+        o.p = nullptr; o.bytes = o.held = 0;
+    }
     DevBuf &operator=(DevBuf &&o) noexcept {
-        if (this != &o) { release(); p = o.p; bytes = o.bytes; o.p = nullptr; o.bytes = 0; }
+        if (this != &o) {
+            release();
+            p = o.p; bytes = o.bytes; held = o.held; device = o.device;
+            o.p = nullptr; o.bytes = o.held = 0;
+        }
         return *this;
     }
     ~DevBuf() { release(); }
     void alloc(size_t b) {
         release();
         if (b == 0) return;
-        hipError_t e = hipMalloc(&p, b);
-        if (e != hipSuccess) {
-            p = nullptr;
-            throw Error(MGRT_E_OOM_PLAN, "hipMalloc of " + std::to_string(b) + " bytes failed: " +
-                                             hipGetErrorString(e));
+        p = cache_take(b, &held);
+        if (!p) {
+            hipError_t e = hipMalloc(&p, b);
+            if (e != hipSuccess && cache_drain()) {
+                (void)hipGetLastError();
+                e = hipMalloc(&p, b);
+            }
+            if (e != hipSuccess) {
+                p = nullptr;
+                throw Error(MGRT_E_OOM_PLAN, "hipMalloc of " + std::to_string(b) + " bytes failed: " +
+                                                 hipGetErrorString(e));
+            }
+            held = b;
         }
         bytes = b;
+        if (hipGetDevice(&device) != hipSuccess) device = -1;
     }
     void release() {
-        if (p) (void)hipFree(p);
+        if (p && !cache_give(p, held, device)) (void)hipFree(p);
         p = nullptr;
-        bytes = 0;
+        bytes = held = 0;
     }
     template <typename T> T *as() const { return static_cast<T *>(p); }
 };
@@ -100,6 +136,34 @@ inline DevBuf upload(const std::vector<T> &v, hipStream_t s) {
     if (!v.empty()) MGRT_HIP(hipMemcpy(b.p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
     return b;
 }
+
+// Several host arrays copied to the device in one piece (a blocking copy costs 13 us whatever
+// its size below 64 KB, and a run hands over ten lists): add() returns an array's offset,
+// 16-byte aligned; upload() copies into the arena when one is given.
+struct Pack {
+    std::vector<char> h;
+    DevBuf own;
+    char *dev = nullptr;
+    template <typename T>
+    size_t add(const std::vector<T> &v) {
+        const size_t off = (h.size() + 15) & ~(size_t)15;
+        h.resize(off + v.size() * sizeof(T));
+        if (!v.empty()) std::memcpy(h.data() + off, v.data(), v.size() * sizeof(T));
+        return off;
+    }
+    void upload(Arena *ar) {
+        const size_t b = std::max<size_t>(16, h.size());
+        h.resize(b);
+        if (ar) {
+            dev = static_cast<char *>(ar->take(b));
+        } else {
+            own.alloc(b);
+            dev = own.as<char>();
+        }
+        MGRT_HIP(hipMemcpy(dev, h.data(), b, hipMemcpyHostToDevice));
+    }
+    template <typename T> T *at(size_t off) const { return reinterpret_cast<T *>(dev + off); }
+};
 
 // P1 point stencil: the d+1 nodes of the containing simplex and the barycentric weights.
 struct Stencil {

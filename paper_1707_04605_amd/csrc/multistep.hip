@@ -825,19 +825,22 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
     GroupLists tp = group_lists(B, groups, run.rec, c.hm.iperm, true, [](const Record &e) { return e.dst; });
     if (!ld.fits || !tp.fits) return false;
     if (run.d_series == nullptr) MGRT_REQUIRE(run.inj.empty(), MGRT_E_ARG, "loads without series");
-    DevBuf lb[5], tb[5], xa, xb, done;
+    Pack pack;
+    size_t lo[5], to[5];
+    DevBuf xa, xb, done;
     const size_t state = (size_t)groups * n * B.vec * sizeof(T);
     const bool strip = B.nx > 0;
     try {
-        auto up = [&](GroupLists &L, DevBuf *d) {
-            d[0] = upload(L.ptr, s);
-            d[1] = upload(L.loc, s);
-            d[2] = upload(L.col, s);
-            d[3] = upload(L.aux, s);
-            d[4] = upload(L.w, s);
+        auto up = [&](GroupLists &L, size_t *o) {
+            o[0] = pack.add(L.ptr);
+            o[1] = pack.add(L.loc);
+            o[2] = pack.add(L.col);
+            o[3] = pack.add(L.aux);
+            o[4] = pack.add(L.w);
         };
-        up(ld, lb);
-        up(tp, tb);
+        up(ld, lo);
+        up(tp, to);
+        pack.upload(nullptr);
         if (!run.d_alt_p) {
             xa.alloc(state);
             xb.alloc(state);
@@ -867,16 +870,16 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
     // one-column runs of small meshes have always summed in this order (their traces are within
     // rounding of the one-step launches', and stay what they were)
     a.beta_first = run.B == 1 && n <= 65536 && !run.hist && !run.d_vel_out && !run.d_acc;
-    a.ld_ptr = lb[0].as<int32_t>();
-    a.ld_loc = lb[1].as<int32_t>();
-    a.ld_col = lb[2].as<int32_t>();
-    a.ld_sid = lb[3].as<int32_t>();
-    a.ld_w = lb[4].as<double>();
-    a.tp_ptr = tb[0].as<int32_t>();
-    a.tp_loc = tb[1].as<int32_t>();
-    a.tp_col = tb[2].as<int32_t>();
-    a.tp_dst = tb[3].as<int32_t>();
-    a.tp_w = tb[4].as<double>();
+    a.ld_ptr = pack.at<int32_t>(lo[0]);
+    a.ld_loc = pack.at<int32_t>(lo[1]);
+    a.ld_col = pack.at<int32_t>(lo[2]);
+    a.ld_sid = pack.at<int32_t>(lo[3]);
+    a.ld_w = pack.at<double>(lo[4]);
+    a.tp_ptr = pack.at<int32_t>(to[0]);
+    a.tp_loc = pack.at<int32_t>(to[1]);
+    a.tp_col = pack.at<int32_t>(to[2]);
+    a.tp_dst = pack.at<int32_t>(to[3]);
+    a.tp_w = pack.at<double>(to[4]);
     a.series = run.d_series;
     a.series_len = run.series_len;
     a.step0 = run.step0;

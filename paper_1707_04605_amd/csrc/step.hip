@@ -304,17 +304,23 @@ StepOp &get_step_op(Ctx &c, int S, int prec, double dt) {
 namespace {
 
 struct TileLists {
-    DevBuf own[5];
+    size_t o[5] = {};
     const int32_t *ptr = nullptr, *loc = nullptr, *col = nullptr, *aux = nullptr;
     const double *w = nullptr;
+    void bind(const Pack &pk) {
+        ptr = pk.at<int32_t>(o[0]);
+        loc = pk.at<int32_t>(o[1]);
+        col = pk.at<int32_t>(o[2]);
+        aux = pk.at<int32_t>(o[3]);
+        w = pk.at<double>(o[4]);
+    }
 };
 
-// Group entries by tile (stable in the given order) and upload (into the arena when one
-// is given).  Entries name nodes by the caller's id; they are placed by stepping order.
+// Group entries by tile (stable in the given order) into the pack.  Entries name nodes by
+// the caller's id; they are placed by stepping order.
 template <typename Ent, typename AuxFn, typename WFn>
 TileLists make_lists(const std::vector<Ent> &ents, int S, int64_t n_tiles,
-                     const std::vector<int32_t> &iperm, AuxFn aux, WFn wfn, hipStream_t s,
-                     Arena *ar) {
+                     const std::vector<int32_t> &iperm, AuxFn aux, WFn wfn, Pack &pk) {
     std::vector<int32_t> ptr(n_tiles + 1, 0);
     for (const auto &e : ents) ptr[iperm[e.node] / S + 1]++;
     for (int64_t t = 0; t < n_tiles; ++t) ptr[t + 1] += ptr[t];
@@ -334,24 +340,11 @@ TileLists make_lists(const std::vector<Ent> &ents, int S, int64_t n_tiles,
         loc.push_back(0); col.push_back(-1); ax.push_back(0); w.push_back(0);
     }
     TileLists L;
-    if (ar) {
-        L.ptr = put(*ar, ptr);
-        L.loc = put(*ar, loc);
-        L.col = put(*ar, col);
-        L.aux = put(*ar, ax);
-        L.w = put(*ar, w);
-        return L;
-    }
-    L.own[0] = upload(ptr, s);
-    L.own[1] = upload(loc, s);
-    L.own[2] = upload(col, s);
-    L.own[3] = upload(ax, s);
-    L.own[4] = upload(w, s);
-    L.ptr = L.own[0].as<int32_t>();
-    L.loc = L.own[1].as<int32_t>();
-    L.col = L.own[2].as<int32_t>();
-    L.aux = L.own[3].as<int32_t>();
-    L.w = L.own[4].as<double>();
+    L.o[0] = pk.add(ptr);
+    L.o[1] = pk.add(loc);
+    L.o[2] = pk.add(col);
+    L.o[3] = pk.add(ax);
+    L.o[4] = pk.add(w);
     return L;
 }
 
@@ -492,16 +485,21 @@ void run_batch_t(Ctx &c, StepOp &op, BatchRun &run) {
     MGRT_REQUIRE(tile_nodes(op.prec, run.B) == S, MGRT_E_ARG, "batch width does not match operator tiles");
     c.timing.steps_per_launch = 1;
     const std::vector<int32_t> &ip = c.hm.iperm;
+    Pack pack;
     TileLists inj = make_lists(run.inj, S, op.n_tiles, ip, [](const Injection &e) { return e.sid; },
-                               [](const Injection &e) { return e.weight; }, s, run.arena);
+                               [](const Injection &e) { return e.weight; }, pack);
     TileLists rec = make_lists(run.rec, S, op.n_tiles, ip, [](const Record &e) { return e.dst; },
-                               [](const Record &e) { return e.weight; }, s, run.arena);
+                               [](const Record &e) { return e.weight; }, pack);
     std::vector<HistEnt> hents;
     if (run.hist)
         for (size_t k = 0; k < run.hist_nodes.size(); ++k)
             hents.push_back(HistEnt{run.hist_nodes[k], 0, (int32_t)k});
     TileLists hl = make_lists(hents, S, op.n_tiles, ip, [](const HistEnt &e) { return e.idx; },
-                              [](const HistEnt &) { return 0.0; }, s, run.arena);
+                              [](const HistEnt &) { return 0.0; }, pack);
+    pack.upload(run.arena);
+    inj.bind(pack);
+    rec.bind(pack);
+    hl.bind(pack);
 
     StepArgs<T> a{};
     a.slice_ptr = op.slice_ptr.as<int64_t>();

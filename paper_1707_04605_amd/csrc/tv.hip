@@ -874,7 +874,7 @@ struct TvSystem {
         // normal matrix when one product with it moves fewer bytes than two passes over L
         // and it fits the free memory
         size_t fr = 0, tot = 0;
-        MGRT_HIP(hipMemGetInfo(&fr, &tot));
+        device_memory(&fr, &tot);
         const double esz = prec == 32 ? 4.0 : 8.0;
         const double gbytes = (double)M * M * 8;
         if (gbytes < 2.0 * rows * M * esz && gbytes + (2ull << 30) < (double)fr) form_normal_matrix();

@@ -84,3 +84,33 @@ def test_jacobian_histories_equal_one_step(mgrt, N, src, prec):
                             batch=t["batch"], **kw)
     assert ctx.last_timing()["steps_per_launch"] == 1
     assert np.array_equal(a, b)
+
+
+# regions with one, two and four columns a group, strips, one tile, 3D regions and 3D one-step
+# launches; batches that leave a ragged one
+@pytest.mark.parametrize("cfg,N,L,src,steps,prec,level", [
+    ("c1", 24, 2, 2, 300, 64, "coarse"), ("c1", 45, 0, 3, 301, 64, "fine"), ("c1", 48, 2, 1, 300, 64, "coarse"),
+    ("c1", 96, 3, 23, 300, 32, "coarse"), ("c1", 300, 2, 33, 263, 32, "fine"), ("c1", 300, 2, 9, 263, 64, "coarse"),
+    ("c4", 12, 1, 4, 300, 64, "coarse"), ("c4", 24, 1, 3, 270, 32, "coarse"), ("c4", 48, 0, 16, 260, 32, "fine")])
+def test_gradient_with_all_velocities_kept(mgrt, cfg, N, L, src, steps, prec, level):
+    """One segment (both sweeps several steps per launch) against checkpointed segments of one
+    step per launch: equal fields, so the gradients differ by the order in which a node adds up
+    its steps' and columns' products, steps * columns * 2^-53 <= 1e-12 of their magnitudes."""
+    p = configs.make(cfg, N=N, L=L, n_src=src, n_steps=steps)
+    rec = p.rec[:, :1]
+    res = np.random.default_rng(5).standard_normal((src, 1, steps))
+    ctx = mgrt.context_for_problem(p)
+    args = (p.src, rec, p.wavelet, p.dt, steps, res, level)
+    a = ctx.misfit_gradient(*args, precision=prec)
+    t = ctx.last_timing()
+    n = p.mesh.coords.shape[0]
+    assert t["node_updates"] == 2 * n * steps * src
+    # enough for states, checkpoints and a segment of about sqrt(2 * steps) steps, not for all
+    slab = n * t["batch"] * (prec // 8)
+    b = ctx.misfit_gradient(*args, precision=prec, batch=t["batch"] if src > 1 else 0, launch=4,
+                            mem_budget_gb=(2 * np.sqrt(2 * steps) + 20) * slab / 2**30)
+    tb = ctx.last_timing()
+    assert tb["steps_per_launch"] == 1 and tb["node_updates"] == 3 * n * steps * src
+    err = float(np.linalg.norm(a - b) / np.linalg.norm(b))
+    print(f"{cfg} N={N} {src} columns prec={prec}: {t['steps_per_launch']} steps per launch, {err:.2e}")
+    assert err <= 1e-12
