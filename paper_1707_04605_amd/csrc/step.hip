@@ -187,17 +187,14 @@ static void fill_values(Ctx &c, StepOp &op) {
             const int64_t t = et[e] / d;
             for (int a = 0; a < NV; ++a) cnt[hm.iperm[hm.elems[t * NV + a]] + 1]++;
         }
-        std::vector<int32_t> node_row(n, -1);
-        std::vector<int32_t> rptr{0};
+        std::vector<int32_t> rptr(n + 1, 0);
         std::vector<int64_t> rstart(n, 0);
-        int64_t nrows = 0, nnz = 0;
-        for (int64_t ii = 0; ii < n; ++ii)
-            if (cnt[ii + 1] > 0) {
-                node_row[ii] = (int32_t)nrows++;
-                rstart[ii] = nnz;
-                nnz += cnt[ii + 1];
-                rptr.push_back((int32_t)nnz);
-            }
+        int64_t nnz = 0;
+        for (int64_t ii = 0; ii < n; ++ii) {
+            rstart[ii] = nnz;
+            nnz += cnt[ii + 1];
+            rptr[ii + 1] = (int32_t)nnz;
+        }
         std::vector<int32_t> rent(nnz);
         std::vector<T> rcoef(nnz);
         std::vector<int64_t> fill(rstart);
@@ -232,13 +229,11 @@ static void fill_values(Ctx &c, StepOp &op) {
         }
         PmlOp &P = op.pml;
         P.n_ent = ne;
-        P.n_rows = nrows;
         P.nnz = nnz;
         P.ent_rec = upload(erec, c.stream);
         P.row_ptr = upload(rptr, c.stream);
         P.row_ent = upload(rent, c.stream);
         P.row_coef = upload(rcoef, c.stream);
-        P.node_row = upload(node_row, c.stream);
     }
     MGRT_HIP(hipStreamSynchronize(c.stream));
 }
@@ -406,7 +401,6 @@ Tuned tune_variant(Ctx &c, const StepOp &op, const StepArgs<T> &proto, int B, in
     a.acc = nullptr;
     a.vel_out = nullptr;
     a.inj_ptr = nullptr;
-    a.pml_row = nullptr;
     hipEvent_t e0, e1;
     MGRT_HIP(hipEventCreate(&e0));
     MGRT_HIP(hipEventCreate(&e1));
@@ -614,14 +608,15 @@ void run_batch_t(Ctx &c, StepOp &op, BatchRun &run) {
             q1.alloc(qbytes);
             q1p = q1.as<T>();
         }
-        a.pml_row = P.node_row.as<int32_t>();
         a.pml_ptr = P.row_ptr.as<int32_t>();
         a.pml_ent = P.row_ent.as<int32_t>();
         a.pml_coef = P.row_coef.as<T>();
+        a.pml_rec = P.ent_rec.as<uint32_t>();
+        a.pml_n_ent = P.n_ent;
+        a.pml_nv = c.hm.d + 1;
+        a.pml_blocks = (int32_t)(((P.n_ent + S - 1) / S + 7) / 8 * 8);     // S = entries a workgroup
     }
     T *qa = run.d_q ? static_cast<T *>(run.d_q) : q0p, *qb_ = q1p;
-    const int pvec = sizeof(T) == 4 ? (run.B >= 4 ? 4 : 1) : (run.B >= 2 ? 2 : 1);
-    const int64_t g_ent = (P.n_ent * (run.B / pvec) + 255) / 256;
     T *bufA = static_cast<T *>(run.d_p);
     T *bufB = static_cast<T *>(run.d_pm);
     const int64_t nB = n * (int64_t)run.B;
@@ -648,9 +643,9 @@ void run_batch_t(Ctx &c, StepOp &op, BatchRun &run) {
         if (P.n_ent > 0) {
             // the step reads q_{l-1/2} (qa) for its load; the update writes q_{l+1/2} (qb_)
             a.pml_q = qa;
-            launch_pml_q<T>(c.hm.d, pvec, P, run.B, g_ent, bufA, qa, qb_, s);
+            a.pml_qn = qb_;
         }
-        launch_step<T>(a, run.B, W, nt, pk, grid, s);
+        launch_step<T>(a, run.B, W, nt, pk, grid + a.pml_blocks, s);
         if (P.n_ent > 0) std::swap(qa, qb_);
         if (flush) {
             hipLaunchKernelGGL(k_hist_flush<T>, dim3((hist_nser + 63) / 64), dim3(256), 0, s,
@@ -735,7 +730,7 @@ void run_batch_t(Ctx &c, StepOp &op, BatchRun &run) {
         // more), entry and row coefficients, the node -> row map
         const double pml_bytes =
             P.n_ent > 0 ? 3.0 * esz * (double)P.n_ent * run.B + (double)P.n_ent * (NV * (4 + esz) + esz) +
-                              (double)P.nnz * (4 + esz) + 4.0 * (P.n_rows + 1) + 4.0 * n
+                              (double)P.nnz * (4 + esz) + 4.0 * (n + 1)
                         : 0.0;
         const double per_launch = words * esz * (double)n * run.B + op.oper_bytes +
                                   (run.d_acc ? 16.0 * n : 0.0) + pml_bytes;
