@@ -163,6 +163,8 @@ __global__ __launch_bounds__(1024) void k_blocks(const BlockArgs<T> a) {
     T *adds = reinterpret_cast<T *>(lcol + BL_CAP);              // [k][BL_CAP]
     const int64_t l0 = a.done[a.slot];
     const int ks = a.ksteps;
+    // a launch's steps lie in one chunk of the history stage
+    [[maybe_unused]] const int64_t hist_l0 = EXT && a.hist_of ? l0 % a.hist_chunk : 0;
     if (blockIdx.x == 0 && tid == 0) a.done[a.slot ^ 1] = l0 + ks;
     // item ranges in XCD order: consecutive workgroups go to different XCDs
     const int nwg = gridDim.x;
@@ -333,7 +335,7 @@ __global__ __launch_bounds__(1024) void k_blocks(const BlockArgs<T> a) {
                 }
                 if constexpr (EXT) {
                     if (hx[j] >= 0) {
-                        const int64_t ho = ((l0 + s) % a.hist_chunk * a.hist_nh + hx[j]) * a.hist_b + (int64_t)g * VEC;
+                        const int64_t ho = ((hist_l0 + s) * a.hist_nh + hx[j]) * a.hist_b + (int64_t)g * VEC;
                         const V vel = -inc * a.inv_dt;
                         *reinterpret_cast<V *>(a.hist + ho) = a.hist_mode == 1 ? vel : out;
                         if (a.hist_mode == 2) *reinterpret_cast<V *>(a.hist2 + ho) = vel;
@@ -823,6 +825,10 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
     const int64_t groups = live_groups(run, B.vec);
     GroupLists ld = group_lists(B, groups, run.inj, c.hm.iperm, false, [](const Injection &e) { return e.sid; });
     GroupLists tp = group_lists(B, groups, run.rec, c.hm.iperm, true, [](const Record &e) { return e.dst; });
+    // strips record histories (at 31-bit offsets) or the velocity field, not both
+    if (B.nx > 0 && run.hist &&
+        (run.d_vel_out || (int64_t)run.hist_nodes.size() * run.B * (int64_t)sizeof(T) >= (1ll << 30)))
+        return false;
     if (!ld.fits || !tp.fits) return false;
     if (run.d_series == nullptr) MGRT_REQUIRE(run.inj.empty(), MGRT_E_ARG, "loads without series");
     Pack pack;
@@ -985,10 +991,16 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
         b.halo = B.k;
         const dim3 grid((unsigned)((b.items + 3) / 4));
         auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, b); };
-        if (ks == 8) ext ? go(k_strips<T, VEC, 8, true>) : go(k_strips<T, VEC, 8, false>);
-        else if (ks == 4) ext ? go(k_strips<T, VEC, 4, true>) : go(k_strips<T, VEC, 4, false>);
-        else if (ks == 2) ext ? go(k_strips<T, VEC, 2, true>) : go(k_strips<T, VEC, 2, false>);
-        else ext ? go(k_strips<T, VEC, 1, true>) : go(k_strips<T, VEC, 1, false>);
+        auto by_ext = [&](auto kc) {
+            constexpr int KS = decltype(kc)::value;
+            if (chunk) go(k_strips<T, VEC, KS, 1>);
+            else if (run.d_vel_out) go(k_strips<T, VEC, KS, 2>);
+            else go(k_strips<T, VEC, KS, 0>);
+        };
+        if (ks == 8) by_ext(std::integral_constant<int, 8>{});
+        else if (ks == 4) by_ext(std::integral_constant<int, 4>{});
+        else if (ks == 2) by_ext(std::integral_constant<int, 2>{});
+        else by_ext(std::integral_constant<int, 1>{});
     };
     auto issue = [&](int64_t ks) {
         a.p = src_p;

@@ -59,13 +59,14 @@ __device__ __forceinline__ double lane_next(double x) {
     return __hiloint2double(hi, lo);
 }
 
-template <typename T, int VEC, int K, bool EXT>
+// EXT: 1 the run records node histories, 2 the velocity field, 0 neither
+template <typename T, int VEC, int K, int EXT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_strips(
     const StripArgs<T> a) {
     typedef typename GroupVec<T, VEC>::type V;
     constexpr int R = K <= 1 ? 1 : K <= 2 ? 2 : K <= 4 ? 4 : 8;
     __shared__ T cf[4][R][5][64];
-    __shared__ int32_t hr[EXT ? 4 : 1][R][64];
+    __shared__ int32_t hr[EXT == 1 ? 4 : 1][R][64];
     __shared__ T adds[4][K][BL_CAP], tapv[4][K][BL_CAP];     // loads of the steps, values of the taps
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t l0 = a.done[a.slot];
@@ -133,6 +134,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     for (int u = 0; u < VEC; ++u) m1[u] = T(0);
     // rows of this item, bit m: row i - 1 - m carries loads / taps / histories
     uint32_t lrows = 0, trows = 0, hrows = 0;
+    // Histories: the values of an iteration's first such row (coarse nodes lie 2^L rows apart,
+    // so there is hardly a second) leave with the iteration's other stores, unconditionally
+    // (OOB where there is none): with stores in branches of the levels the waits for fetched
+    // rows count those too, and a 64-bit remainder per row took its time (513^2 nodes x 32
+    // FP32 columns, coarse nodes 8 apart: 81.7 -> 68.6 us per launch of 8 steps).
+    // A launch's steps lie in one chunk of the stage.
+    constexpr int OOB = (int)0x80000000;
+    const int64_t hrow = EXT == 1 ? a.hist_nh * a.hist_b : 0;
+    const int64_t hb = EXT == 1 ? l0 % a.hist_chunk * hrow : 0;
+    T *const h1 = a.hist + hb, *const h2 = a.hist_mode == 2 ? a.hist2 + hb : nullptr;
+    T *const vel0 = EXT == 2 ? a.vel_out + l0 * a.vel_step + go * VEC : nullptr;
+    V hout, hvel;
+#pragma unroll
+    for (int u = 0; u < VEC; ++u) hout[u] = hvel[u] = T(0);
     auto fetch = [&](auto qc, int i) {
         constexpr int Q = decltype(qc)::value;
         const int y = ya - K + i, yc = min(max(y, 0), a.ny - 1);
@@ -141,8 +156,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         const int64_t rn = (int64_t)yc * a.nx;
         nc[Q] = *reinterpret_cast<const C4 *>(cx + rn * 4);
         nb[Q] = bx[rn];
-        if constexpr (EXT)
-            if (a.hist_of) nh[Q] = a.hist_of[rn + xc];
+        if constexpr (EXT == 1) nh[Q] = a.hist_of[rn + xc];
     };
     const int nit = yb - ya + 2 * K;
     int ifirst = 0;             // iterations up to the last that may see a row of row_first
@@ -183,9 +197,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         cw[4] = in ? nb[Q] : T(0);
 #pragma unroll
         for (int q = 0; q < 5; ++q) asm volatile("" : "+v"(cw[q]));
-        const int hw = EXT && a.hist_of && xown && y >= ya && y < yb ? nh[Q] : -1;
+        const int hw = EXT == 1 && xown && y >= ya && y < yb ? nh[Q] : -1;
         fetch(qc, i + PD);
         V last = m1, lastc = m1;
+        int hat = OOB;
+        [[maybe_unused]] const int hm = __ffs((int)hrows & ((1 << K) - 1)) - 1;
         // a level's coefficients are read one level ahead of their use
         T cv[2][5];
         auto coef = [&](int m) {
@@ -251,20 +267,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
                     if (lane == at) tapv[wave][m][e] = val;
                 }
             }
-            if constexpr (EXT) {
+            if constexpr (EXT == 1) {
                 if (hrows & (1u << m)) {
                     const int hx = hr[wave][slot][lane];
-                    if (hx >= 0) {
-                        const int64_t ho = ((l0 + m) % a.hist_chunk * a.hist_nh + hx) * a.hist_b + (int64_t)g * VEC;
-                        const V vel = -inc * a.inv_dt;
-                        *reinterpret_cast<V *>(a.hist + ho) = a.hist_mode == 1 ? vel : out;
-                        if (a.hist_mode == 2) *reinterpret_cast<V *>(a.hist2 + ho) = vel;
+                    const V vel = -inc * a.inv_dt;
+                    if (m == hm) {
+                        hat = hx >= 0 ? (hx * (int)a.hist_b + g * VEC) * (int)sizeof(T) : OOB;
+                        hout = a.hist_mode == 1 ? vel : out;
+                        hvel = vel;
+                    } else if (hx >= 0) {
+                        const int64_t ho = m * hrow + hx * a.hist_b + (int64_t)g * VEC;
+                        *reinterpret_cast<V *>(h1 + ho) = a.hist_mode == 1 ? vel : out;
+                        if (h2) *reinterpret_cast<V *>(h2 + ho) = vel;
                     }
                 }
-                if (a.vel_out && xown && rr >= K && rr < nit - K)
-                    __builtin_nontemporal_store(
-                        -inc * a.inv_dt, reinterpret_cast<V *>(a.vel_out + (l0 + m) * a.vel_step +
-                                                               (go + (int64_t)(ya - K + rr) * a.nx + xc) * VEC));
+            }
+            if constexpr (EXT == 2) {
+                typedef unsigned int U4 __attribute__((ext_vector_type(4)));
+                T *vp = vel0 + m * a.vel_step;
+                asm volatile("" : "+s"(vp));        // made here: K descriptors kept would spill
+                const auto rv = __builtin_amdgcn_make_buffer_rsrc((void *)vp, 0, bytes, 0x00027000);
+                const int vo = rr >= K && rr < nit - K ? vown : OOB;
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, -inc * a.inv_dt), rv, vo,
+                                                       min(max(ya - K + rr, 0), a.ny - 1) * rowb, 2);
             }
             if (m + 1 < K) {
                 L[m + 1 < K ? m + 1 : 0][Q] = out;
@@ -278,6 +303,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             const int vo = i < 2 * K || i >= nit ? (int)0x80000000 : vown, so = max(y - K, 0) * rowb;
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, last), rop, vo, so, 0);
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, lastc), rom, vo, so, 0);
+            if constexpr (EXT == 1) {
+                const int64_t hs = max(hm, 0) * hrow;
+                const auto r1 = __builtin_amdgcn_make_buffer_rsrc((void *)(h1 + hs), 0, 0x7ffffff0, 0x00027000);
+                const auto r2 = __builtin_amdgcn_make_buffer_rsrc((void *)(h2 ? h2 + hs : h1), 0, 0x7ffffff0, 0x00027000);
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, hout), r1, hat, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, hvel), r2, h2 ? hat : OOB, 0, 0);
+            }
         }
         // row y's coefficients: first used by the next iteration
 #pragma unroll
@@ -285,7 +317,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         m1 = m1n;
         lrows = lrows << 1 | (uint32_t)(__ballot(lloc >> 6 == i) != 0);
         trows = trows << 1 | (uint32_t)(__ballot(tloc >> 6 == i) != 0);
-        if constexpr (EXT) {
+        if constexpr (EXT == 1) {
             hr[wave][i & (R - 1)][lane] = hw;
             hrows = hrows << 1 | (uint32_t)(__ballot(hw >= 0) != 0);
         }

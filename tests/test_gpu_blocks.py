@@ -86,6 +86,20 @@ def test_jacobian_histories_equal_one_step(mgrt, N, src, prec):
     assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("L,prec", [(1, 32), (1, 64), (2, 32)])
+def test_jacobian_histories_in_neighbouring_rows(mgrt, L, prec):
+    """Strips whose launches meet coarse nodes in several of a wave's rows at once."""
+    p = configs.make("c3", N=512, L=L, n_src=16 if prec == 64 else 32, n_steps=270, n_samples=3)
+    ctx = mgrt.context_for_problem(p)
+    kw = dict(mode="mg", precision=prec)
+    a = ctx.jacobian_coarse(p.src, p.rec, p.wavelet, p.dt, p.n_steps, p.sample_steps, **kw)
+    t = ctx.last_timing()
+    assert t["steps_per_launch"] == 8
+    b = ctx.jacobian_coarse(p.src, p.rec, p.wavelet, p.dt, p.n_steps, p.sample_steps, batch=t["batch"], **kw)
+    assert ctx.last_timing()["steps_per_launch"] == 1
+    assert np.array_equal(a, b)
+
+
 # regions with one, two and four columns a group, strips, one tile, 3D regions and 3D one-step
 # launches; batches that leave a ragged one
 @pytest.mark.parametrize("cfg,N,L,src,steps,prec,level", [
