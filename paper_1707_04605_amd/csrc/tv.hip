@@ -73,12 +73,17 @@ __global__ __launch_bounds__(256) void k_colsq_part(const T *__restrict__ L, int
 }
 
 // Normal matrix G = L^T L (FP64) on the matrix cores: v_mfma_f64_16x16x4f64.  One
-// workgroup forms a 64 x 64 block (bi, bj >= bi); each of its 4 waves a 32 x 32 quarter as
-// 2 x 2 MFMA tiles.  L streams through LDS in panels (converted to FP64).
+// workgroup forms a TILE x TILE block (bi, bj >= bi); each of its 4 waves a quarter as
+// (TILE / 32)^2 MFMA tiles.  L streams through LDS in panels (converted to FP64).
 // MFMA operand layout (wave64): lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]
 // of the 16x4 and 4x16 operands and receives D[4 v + l / 16][l % 16] in slot v.
 // Only the upper blocks are formed (the Woodbury row Gram matrix, which needs all of
 // them, is completed by k_mirror_lower).
+//
+// The matrix cores bound it (a large FP64 product of the library's reaches 73 TFLOP/s here):
+// 32,768 x 8,192 FP32 in tiles of 64 50.1 ms, 44 TFLOP/s; of 128 in XCD order 41.0; with the
+// last round in quarters 37.7, 58 TFLOP/s.  Splitting the rows instead (37.3 ms) was left out:
+// an entry's rows are summed in their order, whatever the tile.
 constexpr int SYRK_PAD = 4;
 typedef double d4v __attribute__((ext_vector_type(4)));
 
@@ -86,64 +91,107 @@ typedef double d4v __attribute__((ext_vector_type(4)));
 // matrix cores work on the current one (the loads are in flight during the MFMAs).
 constexpr int SYRK_KT2 = 32;
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_syrk(const T *__restrict__ L, int64_t rows, int64_t M,
-                                              double *__restrict__ G) {
-    const int64_t bi = blockIdx.y, bj = blockIdx.x;
-    if (bj < bi) return;
-    __shared__ double As[SYRK_KT2][64 + SYRK_PAD];
-    __shared__ double Bs[SYRK_KT2][64 + SYRK_PAD];
-    constexpr int PER = SYRK_KT2 * 64 / 256;            // elements per thread per panel
+constexpr int64_t CHOL_GROUP = 4;      // block rows of the factor per update of the rest
+
+// acc += L[r0..r1, i0 + ..]^T L[r0..r1, j0 + ..] for a workgroup's TILE x TILE block;
+// wave (wy, wx) holds the quarter at (TILE / 2 wy, TILE / 2 wx).
+template <typename T, int TILE>
+__device__ __forceinline__ void gram_tile(const T *L, int64_t rb0, int64_t re, int64_t M, int64_t i0, int64_t j0,
+                                          double *sm, d4v (&acc)[TILE / 32][TILE / 32]) {
+    constexpr int KT = TILE == 128 ? SYRK_KT2 / 2 : SYRK_KT2;  // panel rows (registers)
+    constexpr int STR = TILE + 16;                      // 4 rows of 16 doubles: all 64 banks
+    constexpr int NT = TILE / 32;                       // MFMA tiles per wave and direction
+    constexpr int CPR = 256 / TILE;                     // rows a pass of the workgroup loads
+    constexpr int PER = KT / CPR;                       // elements per thread per panel
+    double (*As)[STR] = reinterpret_cast<double (*)[STR]>(sm);
+    double (*Bs)[STR] = As + KT;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int wy = wave >> 1, wx = wave & 1;
-    const int64_t i0 = bi * 64, j0 = bj * 64;
-    const int cc = tid & 63, kr0 = tid >> 6;            // element e = kr0 + 4 u of column cc
+    const int cc = tid % TILE, kr0 = tid / TILE;        // element e = kr0 + CPR u of column cc
     const bool ci = i0 + cc < M, cj = j0 + cc < M;
-    d4v acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = d4v{0.0, 0.0, 0.0, 0.0};
     T ra[PER], rb[PER];
     auto fetch = [&](int64_t r0) {
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-            const int64_t r = r0 + kr0 + 4 * u;
-            ra[u] = (r < rows && ci) ? L[r * M + i0 + cc] : T(0);
-            rb[u] = (r < rows && cj) ? L[r * M + j0 + cc] : T(0);
+            const int64_t r = r0 + kr0 + CPR * u;
+            ra[u] = (r < re && ci) ? L[r * M + i0 + cc] : T(0);
+            rb[u] = (r < re && cj) ? L[r * M + j0 + cc] : T(0);
         }
     };
-    fetch(0);
-    for (int64_t r0 = 0; r0 < rows; r0 += SYRK_KT2) {
+    fetch(rb0);
+    for (int64_t r0 = rb0; r0 < re; r0 += KT) {
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-            As[kr0 + 4 * u][cc] = (double)ra[u];
-            Bs[kr0 + 4 * u][cc] = (double)rb[u];
+            As[kr0 + CPR * u][cc] = (double)ra[u];
+            Bs[kr0 + CPR * u][cc] = (double)rb[u];
         }
         __syncthreads();
-        if (r0 + SYRK_KT2 < rows) fetch(r0 + SYRK_KT2);
+        if (r0 + KT < re) fetch(r0 + KT);
 #pragma unroll
-        for (int kk = 0; kk < SYRK_KT2; kk += 4) {
+        for (int kk = 0; kk < KT; kk += 4) {
             const int kr = kk + (lane >> 4), c16 = lane & 15;
-            const double a0 = As[kr][32 * wy + c16], a1 = As[kr][32 * wy + 16 + c16];
-            const double b0 = Bs[kr][32 * wx + c16], b1 = Bs[kr][32 * wx + 16 + c16];
-            acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
+            double a[NT], b[NT];
+#pragma unroll
+            for (int e = 0; e < NT; ++e) {
+                a[e] = As[kr][16 * (NT * wy + e) + c16];
+                b[e] = Bs[kr][16 * (NT * wx + e) + c16];
+            }
+#pragma unroll
+            for (int ea = 0; ea < NT; ++ea)
+#pragma unroll
+                for (int eb = 0; eb < NT; ++eb)
+                    acc[ea][eb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ea], b[eb], acc[ea][eb], 0, 0, 0);
         }
         __syncthreads();
     }
+}
+
+// f(i, j, x) for the entries x of a wave's accumulators at (i, j) of the block
+template <int NT, typename F>
+__device__ __forceinline__ void each_entry(d4v (&acc)[NT][NT], F f) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < NT; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < NT; ++b)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int64_t i = i0 + 32 * wy + 16 * a + 4 * v + (lane >> 4);
-                const int64_t j = j0 + 32 * wx + 16 * b + (lane & 15);
-                if (i < M && j < M) G[i * M + j] = acc[a][b][v];
+                double x = acc[a][b][v];
+                f(16 * (NT * (wave >> 1) + a) + 4 * v + (lane >> 4), 16 * (NT * (wave & 1) + b) + (lane & 15), x);
+                acc[a][b][v] = x;
             }
+}
+
+// LDS of the panels of tiles up to TILE
+template <int TILE>
+constexpr int gram_lds = 2 * SYRK_KT2 * (TILE == 32 ? 48 : 80);      // 128: 2 * 16 * 144 is less
+
+// Workgroups 0 .. n_main rounded up to 8: the blocks at[0 .. n_main), TILE x TILE (chunks of the
+// list go to one XCD, whose workgroups then read the same columns of L through its L2);
+// behind them the rest of the list, quarters of that.  at: the block's row and column / 32.
+template <typename T, int TILE>
+__global__ __launch_bounds__(256, 2) void k_syrk(const T *__restrict__ L, int64_t rows, int64_t M,
+                                                 const int2 *__restrict__ at, int n_main, double *__restrict__ G) {
+    __shared__ double sm[gram_lds<TILE>];
+    const int per = (n_main + 7) / 8;
+    int e = blockIdx.x;
+    auto block = [&](auto tile) {
+        constexpr int TL = decltype(tile)::value;
+        const int64_t i0 = (int64_t)at[e].x * 32, j0 = (int64_t)at[e].y * 32;
+        d4v acc[TL / 32][TL / 32];
+        each_entry(acc, [](int, int, double &x) { x = 0.0; });
+        gram_tile<T, TL>(L, 0, rows, M, i0, j0, sm, acc);
+        each_entry(acc, [&](int i, int j, double &x) {
+            if (i0 + i < M && j0 + j < M) G[(i0 + i) * M + j0 + j] = x;
+        });
+    };
+    if (e < 8 * per) {
+        e = (e & 7) * per + (e >> 3);
+        if (e < n_main) block(std::integral_constant<int, TILE>{});
+    } else if constexpr (TILE > 32) {
+        e += n_main - 8 * per;
+        block(std::integral_constant<int, TILE / 2>{});
+    }
 }
 
 // G[j][i] = G[i][j] for the blocks below the diagonal, through an LDS transpose
@@ -171,114 +219,175 @@ __global__ __launch_bounds__(256) void k_mirror_lower(double *__restrict__ G, in
 // U_kj = U_kk^-T A_kj, update the trailing upper blocks A_ij -= U_ki^T U_kj (FP64 MFMA).
 // Entries past M act as the identity (the ragged last block).
 
-// Diagonal block k: A_kk = U_kk^T U_kk right-looking over its 64 rows, then X = U_kk^-1 by
-// back substitution on I (row oriented); X goes to Uinv[k] and its transpose to UinvT[k].
+// Diagonal block k: A_kk = U_kk^T U_kk, and Y = U_kk^-T from the same eliminations on I;
+// X = Y^T = U_kk^-1 goes to Uinv[k] and Y to UinvT[k].
 // A pivot that is not finite or not above CHOL_PIV_TOL times the matrix's original
 // diagonal entry (the system is then singular to working precision) sets *flag and the
 // block continues with pivot 1 (every later kernel stays finite); the caller then
 // discards the factor.
+//
+// The chain of 64 pivots bounds it.  Block and I lie in LDS; wave 0 takes 16 rows at a time,
+// lane j with column j of both in registers: a pivot's row is scaled and subtracted from the
+// rows below within the wave (factors by v_readlane, no barrier), which makes the rows of U
+// right of the diagonal tile as well.  All waves then take the 16 rows out of the tiles
+// below on the matrix cores: 8 barriers a block instead of 256
+// (99 -> 18 us).
 constexpr double CHOL_PIV_TOL = 1e-13;
 
-__global__ __launch_bounds__(256) void k_chol_diag(double *__restrict__ A, int64_t M, int64_t k,
+__device__ __forceinline__ double lane_of(double v, int lane) {
+    const int2 w = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(w.x, lane),
+                                                __builtin_amdgcn_readlane(w.y, lane)));
+}
+
+__global__ __launch_bounds__(512) void k_chol_diag(double *__restrict__ A, int64_t M, int64_t k,
                                                    const double *__restrict__ diag0,
                                                    double *__restrict__ Uinv,
                                                    double *__restrict__ UinvT, int *__restrict__ flag) {
-    // thread (q, j) = (tid / 64, tid % 64) keeps entries (i, j), i = q + 4 m, of the block
-    // (r: the factor, x: the inverse) in registers; only the pivot row, and in the inverse
-    // phase one row of X and one column of U, go through LDS (broadcast reads).  One
-    // reciprocal square root per pivot gives U_pp and 1 / U_pp (no division on the
-    // serial chain); the inverse phase reuses the reciprocals.
-    __shared__ double prow[64];
-    __shared__ double pcol[64];
-    __shared__ double d0s[64];                 // the original diagonal of this block
-    __shared__ double rinv[64];                // 1 / U_pp
-    const int tid = threadIdx.x, j = tid & 63, q = tid >> 6;
+    constexpr int STR = 66;                    // columns are read with two lanes a bank
+    __shared__ double S[64][STR];              // A_kk, then U_kk (upper triangle)
+    __shared__ double Y[64][STR];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t o = k * 64;
-    if (tid < 64) d0s[tid] = o + tid < M ? diag0[o + tid] : 1.0;
-    double r[16], x[16];
+    const double d0 = o + lane < M ? diag0[o + lane] : 1.0;
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
-        const int i = q + 4 * m;
-        r[m] = j >= i ? (o + j < M ? A[(o + i) * M + o + j] : (i == j ? 1.0 : 0.0)) : 0.0;
-        x[m] = i == j ? 1.0 : 0.0;
+    for (int m = 0; m < 8; ++m) {
+        const int i = wave + 8 * m;
+        S[i][lane] = lane >= i ? (o + lane < M ? A[(o + i) * M + o + lane] : (i == lane ? 1.0 : 0.0)) : 0.0;
+        Y[i][lane] = i == lane ? 1.0 : 0.0;
+    }
+    __syncthreads();
+    for (int b = 0; b < 4; ++b) {
+        const int o16 = 16 * b;
+        if (wave == 0) {
+            double r[16], x[16];
+#pragma unroll
+            for (int m = 0; m < 16; ++m) {
+                r[m] = S[o16 + m][lane];
+                x[m] = Y[o16 + m][lane];
+            }
+            // Entries left of the diagonal are not read.  A pivot's root is taken while the
+            // previous pivot's row goes out of the rows below; the scheduler keeps to one
+            // pivot at a time (it would otherwise fetch many rows' factors and spill them).
+            double d, inv;
+            bool ok, bad = false;
+            auto root = [&](double v, int at) {
+                d = lane_of(v, at);
+                ok = isfinite(d) & (d > CHOL_PIV_TOL * lane_of(d0, at)) & (d > 0.0);
+                const double w = rsqrt(d);
+                inv = ok ? w : 1.0;
+                bad |= !ok;
+            };
+            root(r[0], o16);
+#pragma unroll
+            for (int p = 0; p < 16; ++p) {
+                const double up = ok ? d * inv : 1.0;
+                r[p] = lane == o16 + p ? up : r[p] * inv;
+                x[p] *= inv;
+#pragma unroll
+                for (int i = p + 1; i < 16; ++i) {
+                    const double u = lane_of(r[p], o16 + i);
+                    r[i] -= u * r[p];
+                    x[i] -= u * x[p];
+                    if (i == p + 1) root(r[i], o16 + i);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int m = 0; m < 16; ++m) {
+                S[o16 + m][lane] = r[m];
+                Y[o16 + m][lane] = x[m];
+            }
+            if (bad && lane == 0) *flag = 1;
+        }
+        __syncthreads();
+        // tiles (i, j) below: j = i .. 3 of A and j = 0 .. b of Y
+        int t = 0;
+        for (int i = b + 1; i < 4; ++i)
+            for (int e = i; e < 5 + b; ++e, ++t) {
+                if ((t & 7) != wave) continue;
+                double (*W)[STR] = e < 4 ? S : Y;
+                const int c = 16 * (e < 4 ? e : e - 4) + (lane & 15), rr = 16 * i + (lane >> 4);
+                d4v acc;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[v] = W[rr + 4 * v][c];
+#pragma unroll
+                for (int kk = 0; kk < 16; kk += 4) {
+                    const int kr = o16 + kk + (lane >> 4);
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-S[kr][16 * i + (lane & 15)], W[kr][c], acc, 0, 0, 0);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) W[rr + 4 * v][c] = acc[v];
+            }
+        __syncthreads();
     }
 #pragma unroll
-    for (int p = 0; p < 64; ++p) {
-        if (q == (p & 3)) prow[j] = r[p >> 2];
-        __syncthreads();
-        const double d = prow[p];
-        const bool ok = isfinite(d) && d > CHOL_PIV_TOL * d0s[p] && d > 0.0;
-        const double inv = ok ? rsqrt(d) : 1.0;
-        const double rp = ok ? d * inv : 1.0;
-        if (tid == 0) {
-            rinv[p] = inv;
-            if (!ok) *flag = 1;
-        }
-        const double uj = j == p ? rp : prow[j] * inv;         // U[p][j], j >= p
-        if (q == (p & 3) && j >= p) r[p >> 2] = uj;
-#pragma unroll
-        for (int m = 0; m < 16; ++m) {
-            const int i = q + 4 * m;
-            if (i > p && i <= j) r[m] -= (prow[i] * inv) * uj;
-        }
-        __syncthreads();
-    }
-    // X = U^-1: back substitution on I, rows mm = 63 .. 0
-#pragma unroll
-    for (int mm = 63; mm >= 0; --mm) {
-        if (j == mm) {
-#pragma unroll
-            for (int m = 0; m < 16; ++m) pcol[q + 4 * m] = q + 4 * m <= mm ? r[m] : 0.0;
-        }
-        if (q == (mm & 3)) {
-            x[mm >> 2] *= rinv[mm];
-            prow[j] = x[mm >> 2];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int m = 0; m < 16; ++m)
-            if (q + 4 * m < mm) x[m] -= pcol[q + 4 * m] * prow[j];
-        __syncthreads();
-    }
-#pragma unroll
-    for (int m = 0; m < 16; ++m) {
-        const int i = q + 4 * m;
-        if (j >= i && o + j < M) A[(o + i) * M + o + j] = r[m];
-        Uinv[k * 4096 + i * 64 + j] = x[m];
-        UinvT[k * 4096 + j * 64 + i] = x[m];
+    for (int m = 0; m < 8; ++m) {
+        const int i = wave + 8 * m;
+        if (lane >= i && o + lane < M) A[(o + i) * M + o + lane] = S[i][lane];
+        UinvT[k * 4096 + i * 64 + lane] = lane <= i ? Y[i][lane] : 0.0;
+        Uinv[k * 4096 + i * 64 + lane] = lane >= i ? Y[lane][i] : 0.0;
     }
 }
 
-// C = X^T Y for 64 x 64 blocks on the matrix cores (the k_syrk operand layout), X and Y
-// 64 rows deep, in two panels of 32 rows (the second loaded while the first is used).
-// mode 0 (row panel): X = U_kk^-1, Y = A_kj, A_kj = C for j = k + 1 + x.
-// mode 1 (trailing update): X = U_ki, Y = U_kj, A_ij -= C for k < i <= j.
-__global__ __launch_bounds__(256) void k_chol_xty(double *__restrict__ A, int64_t M, int64_t k,
-                                                  const double *__restrict__ Uinv, int mode) {
-    const int64_t j = k + 1 + blockIdx.x;
-    const int64_t i = mode == 0 ? k : k + 1 + blockIdx.y;
-    if (j < i) return;
+// Forward substitution step k of U^T y = b (b's later blocks are updated in place): every
+// workgroup forms y_k = U_kk^-T b_k, the first stores it, and workgroup w subtracts
+// U_kj^T y_k from b_j, j = k + 1 + w.  Sums in a fixed order.
+__device__ void chol_fwd(const double *__restrict__ A, int64_t M, int64_t k, const double *__restrict__ Uinv,
+                         double *__restrict__ b, double *__restrict__ y, int w) {
+    __shared__ double ys[64];
+    __shared__ double red[4][64];
+    const int tid = threadIdx.x, cidx = tid & 63, part = tid >> 6;
+    const int64_t o = k * 64;
+    const int64_t col = (k + 1 + w) * 64 + cidx;
+    double s = 0.0, u[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const int m = part * 16 + e;
+        u[e] = col < M && o + m < M ? A[(o + m) * M + col] : 0.0;
+    }
+#pragma unroll
+    for (int m = part * 16; m < part * 16 + 16; ++m)
+        s += Uinv[k * 4096 + m * 64 + cidx] * (o + m < M ? b[o + m] : 0.0);
+    red[part][cidx] = s;
+    __syncthreads();
+    if (tid < 64) ys[cidx] = ((red[0][cidx] + red[1][cidx]) + red[2][cidx]) + red[3][cidx];
+    __syncthreads();
+    if (w == 0 && tid < 64 && o + cidx < M) y[o + cidx] = ys[cidx];
+    double t = 0.0;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) t += u[e] * ys[part * 16 + e];
+    red[part][cidx] = t;
+    __syncthreads();
+    if (tid < 64 && col < M) b[col] -= ((red[0][cidx] + red[1][cidx]) + red[2][cidx]) + red[3][cidx];
+}
+
+__global__ __launch_bounds__(256) void k_chol_fwd(const double *__restrict__ A, int64_t M, int64_t k,
+                                                  const double *__restrict__ Uinv,
+                                                  double *__restrict__ b, double *__restrict__ y) {
+    chol_fwd(A, M, k, Uinv, b, y, blockIdx.x);
+}
+
+// Row panel: A_kj = U_kk^-T A_kj for j = k + 1 + x, on the matrix cores (the k_syrk operand
+// layout) in two panels of 32 rows (the second loaded while the first is used).
+__global__ __launch_bounds__(256) void k_chol_panel(double *__restrict__ A, int64_t M, int64_t k,
+                                                    const double *__restrict__ Uinv) {
     __shared__ double As[SYRK_KT2][64 + SYRK_PAD];
     __shared__ double Bs[SYRK_KT2][64 + SYRK_PAD];
     constexpr int PER = SYRK_KT2 * 64 / 256;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int wy = wave >> 1, wx = wave & 1;
-    const int64_t o = k * 64, i0 = i * 64, j0 = j * 64;
+    const int64_t o = k * 64, j0 = (k + 1 + blockIdx.x) * 64;
     const int cc = tid & 63, kr0 = tid >> 6;
     d4v acc[2][2];
-#pragma unroll
-    for (int ta = 0; ta < 2; ++ta)
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb) acc[ta][tb] = d4v{0.0, 0.0, 0.0, 0.0};
+    each_entry(acc, [](int, int, double &x) { x = 0.0; });
     double ra[PER], rb[PER];
     auto fetch = [&](int r0) {
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             const int m = r0 + kr0 + 4 * u;
-            const int64_t r = o + m;
-            if (mode == 0) ra[u] = Uinv[k * 4096 + m * 64 + cc];
-            else ra[u] = (r < M && i0 + cc < M) ? A[r * M + i0 + cc] : 0.0;
-            rb[u] = (r < M && j0 + cc < M) ? A[r * M + j0 + cc] : 0.0;
+            ra[u] = Uinv[k * 4096 + m * 64 + cc];
+            rb[u] = j0 + cc < M ? A[(o + m) * M + j0 + cc] : 0.0;
         }
     };
     fetch(0);
@@ -303,47 +412,50 @@ __global__ __launch_bounds__(256) void k_chol_xty(double *__restrict__ A, int64_
         }
         __syncthreads();
     }
-#pragma unroll
-    for (int ta = 0; ta < 2; ++ta)
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int64_t gi = i0 + 32 * wy + 16 * ta + 4 * v + (lane >> 4);
-                const int64_t gj = j0 + 32 * wx + 16 * tb + (lane & 15);
-                if (gi < M && gj < M) {
-                    if (mode == 0) A[gi * M + gj] = acc[ta][tb][v];
-                    else A[gi * M + gj] -= acc[ta][tb][v];
-                }
-            }
+    each_entry(acc, [&](int i, int jj, double &x) {
+        if (j0 + jj < M) A[(o + i) * M + j0 + jj] = x;
+    });
 }
 
-// Forward substitution step k of U^T y = b (b's later blocks are updated in place): every
-// workgroup forms y_k = U_kk^-T b_k, the first stores it, and workgroup w subtracts
-// U_kj^T y_k from b_j, j = k + 1 + w.  Sums in a fixed order.
-__global__ __launch_bounds__(256) void k_chol_fwd(const double *__restrict__ A, int64_t M, int64_t k,
-                                                  const double *__restrict__ Uinv,
-                                                  double *__restrict__ b, double *__restrict__ y) {
-    __shared__ double ys[64];
-    __shared__ double red[4][64];
-    const int tid = threadIdx.x, cidx = tid & 63, part = tid >> 6;
-    const int64_t o = k * 64;
-    double s = 0.0;
-    for (int m = part * 16; m < part * 16 + 16; ++m)
-        s += Uinv[k * 4096 + m * 64 + cidx] * (o + m < M ? b[o + m] : 0.0);
-    red[part][cidx] = s;
-    __syncthreads();
-    if (tid < 64) ys[cidx] = ((red[0][cidx] + red[1][cidx]) + red[2][cidx]) + red[3][cidx];
-    __syncthreads();
-    if (blockIdx.x == 0 && tid < 64 && o + cidx < M) y[o + cidx] = ys[cidx];
-    const int64_t col = (k + 1 + blockIdx.x) * 64 + cidx;
-    double t = 0.0;
-    if (col < M)
-        for (int m = part * 16; m < part * 16 + 16; ++m)
-            if (o + m < M) t += A[(o + m) * M + col] * ys[m];
-    red[part][cidx] = t;
-    __syncthreads();
-    if (tid < 64 && col < M) b[col] -= ((red[0][cidx] + red[1][cidx]) + red[2][cidx]) + red[3][cidx];
+// Update of blocks right of and below block k by the rows of blocks kd .. k:
+// A_ij -= sum U_ki^T U_kj in TILE x TILE tiles (ti, tj), ti < ty, ti <= tj < tx: the first n_main
+// of them whole, the others as quarters.  The first n_fwd workgroups take the forward
+// substitution's step k along.
+// A step of 64 rows read and wrote the whole remaining matrix for 64 multiplications an entry
+// and was bound by that (8,192 unknowns: 9.0 ms of panels and updates a factor).  Now the
+// blocks go in groups of CHOL_GROUP: inside a group a block row is updated by the group's
+// earlier rows when its turn comes, the rest of the matrix once a group, by all its rows.
+// 8,192 unknowns: panels and updates 9.0 -> 6.2 ms a factor (groups of two 7.9).
+template <int TILE>
+__global__ __launch_bounds__(256, 2) void k_chol_update(double *A, int64_t M, int64_t kd, int64_t k, int n_fwd,
+                                                        int n_main, int ty, int tx, const double *__restrict__ Uinv,
+                                                        double *__restrict__ b, double *__restrict__ y) {
+    __shared__ double sm[gram_lds<TILE>];
+    if ((int)blockIdx.x < n_fwd) {
+        chol_fwd(A, M, k, Uinv, b, y, blockIdx.x);
+        return;
+    }
+    auto block = [&](auto tile, int ti, int tj) {
+        constexpr int TL = decltype(tile)::value;
+        const int64_t i0 = (k + 1) * 64 + (int64_t)ti * TL, j0 = (k + 1) * 64 + (int64_t)tj * TL;
+        // the products are summed by themselves, then taken from A_ij in one rounding
+        d4v acc[TL / 32][TL / 32];
+        each_entry(acc, [](int, int, double &x) { x = 0.0; });
+        gram_tile<double, TL>(A, kd * 64, (k + 1) * 64, M, i0, j0, sm, acc);
+        each_entry(acc, [&](int i, int j, double &x) {
+            if (i0 + i < M && j0 + j < M) A[(i0 + i) * M + j0 + j] -= x;
+        });
+    };
+    const int e = blockIdx.x - n_fwd, q = e - n_main;
+    int t = e < n_main ? e : n_main + (q >> 2), ti = 0;
+    while (ti + 1 < ty && t >= tx - ti) t -= tx - ti++;       // row ti holds tiles ti .. tx - 1
+    const int tj = ti + t;
+    if (e < n_main) {
+        block(std::integral_constant<int, TILE>{}, ti, tj);
+    } else if constexpr (TILE > 32) {
+        const int si = 2 * ti + (q >> 1 & 1), sj = 2 * tj + (q & 1);
+        if (si <= sj) block(std::integral_constant<int, TILE / 2>{}, si, sj);
+    }
 }
 
 // Back substitution step k of U z = y (y's earlier blocks are updated in place): every
@@ -357,7 +469,13 @@ __global__ __launch_bounds__(256) void k_chol_bwd(const double *__restrict__ A, 
     __shared__ double ub[64][65];
     const int tid = threadIdx.x, cidx = tid & 63, part = tid >> 6;
     const int64_t o = k * 64;
+    const int64_t i = blockIdx.x;
+    double u[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+        u[e] = i < k && o + cidx < M ? A[(i * 64 + part + 4 * e) * M + o + cidx] : 0.0;
     double s = 0.0;
+#pragma unroll
     for (int m = part * 16; m < part * 16 + 16; ++m)
         s += UinvT[k * 4096 + m * 64 + cidx] * (o + m < M ? y[o + m] : 0.0);
     red[part][cidx] = s;
@@ -365,14 +483,12 @@ __global__ __launch_bounds__(256) void k_chol_bwd(const double *__restrict__ A, 
     if (tid < 64) zs[cidx] = ((red[0][cidx] + red[1][cidx]) + red[2][cidx]) + red[3][cidx];
     __syncthreads();
     if (blockIdx.x == 0 && tid < 64 && o + cidx < M) z[o + cidx] = zs[cidx];
-    const int64_t i = blockIdx.x;
     if (i >= k) return;
-    for (int e = tid; e < 64 * 64; e += 256) {
-        const int ra = e >> 6, cb = e & 63;
-        ub[ra][cb] = (o + cb < M) ? A[(i * 64 + ra) * M + o + cb] : 0.0;
-    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) ub[part + 4 * e][cidx] = u[e];
     __syncthreads();
     double t = 0.0;
+#pragma unroll
     for (int m = part * 16; m < part * 16 + 16; ++m) t += ub[cidx][m] * zs[m];
     red[part][cidx] = t;
     __syncthreads();
@@ -938,16 +1054,47 @@ struct TvSystem {
     DevBuf sym_pairs, sym_part;
     int64_t n_pairs = 0;
 
+    // G's upper 64 x 64 blocks = L^T L (those on the diagonal whole), in the largest tile of 128
+    // (half the reads of L), 64 and 32 that gives every CU a workgroup (two of 128); the
+    // remainder of whole rounds of 256 goes as quarters (16,384 x 2,048 FP64, 528 tiles of 64:
+    // 2.15 -> 1.70 ms).
+    template <typename T>
+    void gram(const T *X, int64_t nr, int64_t nc, double *G) {
+        auto blocks = [&](int64_t t) { return ((nc + t - 1) / t) * ((nc + t - 1) / t + 1) / 2; };
+        const int tile = blocks(128) >= 512 ? 128 : blocks(64) >= 256 ? 64 : 32;
+        const int64_t nb = (nc + tile - 1) / tile;
+        std::vector<int2> at;
+        for (int64_t si = 0; si < nb; si += 8)             // squares of 8 x 8 blocks
+            for (int64_t sj = si; sj < nb; sj += 8)
+                for (int64_t bi = si; bi < std::min(nb, si + 8); ++bi)
+                    for (int64_t bj = std::max(tile == 32 ? bi & ~1 : bi, sj); bj < std::min(nb, sj + 8); ++bj)
+                        at.push_back(make_int2((int)(bi * tile / 32), (int)(bj * tile / 32)));
+        const int n_main = (int)(tile == 32 ? at.size() : at.size() / 256 * 256);
+        const std::vector<int2> rest(at.begin() + n_main, at.end());
+        at.resize(n_main);
+        for (const int2 &b : rest)
+            for (int q = 0; q < 4; ++q) {
+                const int h = tile / 64;
+                const int2 e = make_int2(b.x + (q >> 1) * h, b.y + (q & 1) * h);
+                if (e.x / 2 <= e.y / 2 && 32 * e.y < nc) at.push_back(e);
+            }
+        DevBuf da = upload(at, c.stream);
+        const dim3 grid((n_main + 7) / 8 * 8 + (int)at.size() - n_main);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, grid, dim3(256), 0, c.stream, X, nr, nc, da.as<int2>(), n_main, G);
+        };
+        if (tile == 128) go(k_syrk<T, 128>);
+        else if (tile == 64) go(k_syrk<T, 64>);
+        else go(k_syrk<T, 32>);
+        MGRT_HIP(hipGetLastError());
+        MGRT_HIP(hipStreamSynchronize(c.stream));              // da is freed on return
+    }
+
     void form_normal_matrix() {
         Gm.alloc((size_t)M * M * 8);
         const int64_t nb = (M + 63) / 64;
-        if (prec == 32)
-            hipLaunchKernelGGL(k_syrk<float>, dim3(nb, nb), dim3(256), 0, c.stream,
-                               static_cast<const float *>(L), rows, M, Gm.as<double>());
-        else
-            hipLaunchKernelGGL(k_syrk<double>, dim3(nb, nb), dim3(256), 0, c.stream,
-                               static_cast<const double *>(L), rows, M, Gm.as<double>());
-        MGRT_HIP(hipGetLastError());
+        if (prec == 32) gram(static_cast<const float *>(L), rows, M, Gm.as<double>());
+        else gram(static_cast<const double *>(L), rows, M, Gm.as<double>());
         std::vector<int2> pr;
         for (int64_t bi = 0; bi < nb; ++bi)
             for (int64_t bj = bi; bj < nb; ++bj) pr.push_back(make_int2((int)bi, (int)bj));
@@ -999,8 +1146,7 @@ struct TvSystem {
             hipLaunchKernelGGL(k_scaled_transpose<double>, tg, dim3(256), 0, c.stream,
                                static_cast<const double *>(L), rows, M, dsc.as<double>(), Lt.as<double>());
         const int64_t nb = (rows + 63) / 64;
-        hipLaunchKernelGGL(k_syrk<double>, dim3(nb, nb), dim3(256), 0, c.stream,
-                           static_cast<const double *>(Lt.as<double>()), M, rows, Sg.as<double>());
+        gram(static_cast<const double *>(Lt.as<double>()), M, rows, Sg.as<double>());
         hipLaunchKernelGGL(k_mirror_lower, dim3(nb, nb), dim3(256), 0, c.stream, Sg.as<double>(), rows);
         MGRT_HIP(hipGetLastError());
         std::vector<double> S((size_t)rows * rows);
@@ -1092,32 +1238,46 @@ struct TvSystem {
                 MGRT_HIP(hipStreamSynchronize(c.stream));   // di, dv are freed on return
             }
         }
+        MGRT_HIP(hipMemcpyAsync(wv.p, b, (size_t)M * 8, hipMemcpyDeviceToDevice, c.stream));
         MGRT_HIP(hipMemsetAsync(cflag.p, 0, sizeof(int), c.stream));
         double *A = Am.as<double>();
         hipLaunchKernelGGL(k_get_diag, dim3(g(M)), dim3(256), 0, c.stream, static_cast<const double *>(A), M,
                            dg0.as<double>());
         for (int64_t k = 0; k < nb; ++k) {
-            hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, c.stream, A, M, k,
+            hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(512), 0, c.stream, A, M, k,
                                static_cast<const double *>(dg0.as<double>()), Uinv.as<double>(),
                                UinvT.as<double>(), cflag.as<int>());
-            const int64_t rest = nb - k - 1;
-            if (rest > 0) {
-                hipLaunchKernelGGL(k_chol_xty, dim3(rest), dim3(256), 0, c.stream, A, M, k,
-                                   static_cast<const double *>(Uinv.as<double>()), 0);
-                hipLaunchKernelGGL(k_chol_xty, dim3(rest, rest), dim3(256), 0, c.stream, A, M, k,
-                                   static_cast<const double *>(Uinv.as<double>()), 1);
+            const int rest = (int)(nb - k - 1);
+            const double *ui = Uinv.as<double>();
+            double *w = wv.as<double>(), *yy = yv.as<double>();
+            if (rest == 0) {
+                hipLaunchKernelGGL(k_chol_fwd, dim3(1), dim3(256), 0, c.stream, static_cast<const double *>(A), M, k,
+                                   ui, w, yy);
+                break;
             }
+            hipLaunchKernelGGL(k_chol_panel, dim3(rest), dim3(256), 0, c.stream, A, M, k, ui);
+            const int64_t kd = k - k % CHOL_GROUP;
+            if (k % CHOL_GROUP != CHOL_GROUP - 1) {       // the next block row alone
+                hipLaunchKernelGGL(k_chol_update<32>, dim3(rest + 4 * rest - 1), dim3(256), 0, c.stream, A, M, kd, k,
+                                   rest, 4 * rest - 1, 2, 2 * rest, ui, w, yy);
+                continue;
+            }
+            // as in gram(): whole rounds of 256 tiles, the remainder as quarters
+            const int tile = rest >= 64 ? 128 : rest >= 23 ? 64 : 32, t = (rest * 64 + tile - 1) / tile;
+            const int tiles = t * (t + 1) / 2, n_main = tile == 32 ? tiles : tiles / 256 * 256;
+            const dim3 grid(rest + n_main + 4 * (tiles - n_main));
+            auto go = [&](auto kern) {
+                hipLaunchKernelGGL(kern, grid, dim3(256), 0, c.stream, A, M, kd, k, rest, n_main, t, t, ui, w, yy);
+            };
+            if (tile == 128) go(k_chol_update<128>);
+            else if (tile == 64) go(k_chol_update<64>);
+            else go(k_chol_update<32>);
         }
         MGRT_HIP(hipGetLastError());
         int bad = 0;
         MGRT_HIP(hipMemcpyAsync(&bad, cflag.p, sizeof(int), hipMemcpyDeviceToHost, c.stream));
         MGRT_HIP(hipStreamSynchronize(c.stream));
         if (bad) return false;
-        MGRT_HIP(hipMemcpyAsync(wv.p, b, (size_t)M * 8, hipMemcpyDeviceToDevice, c.stream));
-        for (int64_t k = 0; k < nb; ++k)
-            hipLaunchKernelGGL(k_chol_fwd, dim3(std::max<int64_t>(1, nb - k - 1)), dim3(256), 0, c.stream,
-                               static_cast<const double *>(A), M, k,
-                               static_cast<const double *>(Uinv.as<double>()), wv.as<double>(), yv.as<double>());
         for (int64_t k = nb - 1; k >= 0; --k)
             hipLaunchKernelGGL(k_chol_bwd, dim3(std::max<int64_t>(1, k)), dim3(256), 0, c.stream,
                                static_cast<const double *>(A), M, k,
