@@ -1020,13 +1020,17 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
     auto flush = [&](int64_t count) {
         hist_flush(run, op.prec, st1.p, st2.p, hist_nser, count, a.done + slot, s);
     };
-    // cnt steps as launches of at most k, none of them across a history chunk
+    // steps of the launch after l of cnt steps: at most k, none of them across a history chunk
+    auto next_steps = [&](int64_t l, int64_t cnt) {
+        int64_t ks = std::min<int64_t>(B.k, cnt - l);
+        if (chunk) ks = std::min(ks, chunk - l % chunk);
+        if (strip)
+            while (ks != B.k && (ks & (ks - 1))) ks &= ks - 1;      // k or a power of two
+        return ks;
+    };
     auto steps = [&](int64_t cnt) {
         for (int64_t l = 0; l < cnt;) {
-            int64_t ks = std::min<int64_t>(B.k, cnt - l);
-            if (chunk) ks = std::min(ks, chunk - l % chunk);
-            if (strip)
-                while (ks & (ks - 1)) ks &= ks - 1;      // a power of two
+            const int64_t ks = next_steps(l, cnt);
             issue(ks);
             l += ks;
             if (chunk && (l % chunk == 0 || l == cnt)) flush(l % chunk ? l % chunk : chunk);
@@ -1039,7 +1043,9 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
     int64_t l = 0;
     const int64_t kk = B.k;
     int64_t per = chunk ? chunk : run.B == 1 ? 64 * kk : 64;
-    if (((per + kk - 1) / kk) & 1) per *= 2;
+    int64_t odd = 0;                       // launches of a captured run, as steps() issues them
+    for (int64_t q = 0; q < per; ++odd) q += next_steps(q, per);
+    if (odd & 1) per *= 2;
     const int64_t nrep = run.n_steps / per;
     if (!(run.flags & MGRT_F_NO_GRAPH) && nrep >= 2) {
         hipGraph_t graph = nullptr;

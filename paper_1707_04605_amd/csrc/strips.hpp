@@ -88,15 +88,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const int lb = a.ld_ptr[li], nl = a.ld_ptr[li + 1] - lb;
     const int qb = a.tp_ptr[li], nq = a.tp_ptr[li + 1] - qb;
 
-    // buffer addressing: the row is a scalar offset, the lane's part a constant register, and
+    // buffer addressing: a load's row is a scalar offset, the lane's part a constant register, and
     // a store past the buffer's end is dropped, so the loads and stores of an iteration have
-    // no branches around them and the waits for a row loaded PD iterations ago count exactly
+    // no branches around them and the waits for a row loaded PD iterations ago count exactly.
+    // Stores have no scalar offset: a store of 16 bytes per lane reads its data registers over
+    // several cycles, and the compiler keeps the next write of them off only for stores without
+    // one (with one, lanes 12 to 15 of every 16 got the next value now and then).
+    constexpr int OOB = (int)0x80000000;
     const int rowb = a.nx * 16, bytes = (int)(a.n * 16);
     const auto rp = __builtin_amdgcn_make_buffer_rsrc((void *)gp, 0, bytes, 0x00027000);
     const auto rq = __builtin_amdgcn_make_buffer_rsrc((void *)gq, 0, bytes, 0x00027000);
     const auto rop = __builtin_amdgcn_make_buffer_rsrc((void *)op, 0, bytes, 0x00027000);
     const auto rom = __builtin_amdgcn_make_buffer_rsrc((void *)om, 0, bytes, 0x00027000);
-    const int vin = xc * 16, vown = xown ? xc * 16 : (int)0x80000000;
+    const int vin = xc * 16, vown = xown ? xc * 16 : OOB;
     const T *cx = a.coef + (int64_t)xc * 4, *bx = a.beta + xc;
 
     constexpr int PD = 3;
@@ -140,7 +144,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     // rows count those too, and a 64-bit remainder per row took its time (513^2 nodes x 32
     // FP32 columns, coarse nodes 8 apart: 81.7 -> 68.6 us per launch of 8 steps).
     // A launch's steps lie in one chunk of the stage.
-    constexpr int OOB = (int)0x80000000;
     const int64_t hrow = EXT == 1 ? a.hist_nh * a.hist_b : 0;
     const int64_t hb = EXT == 1 ? l0 % a.hist_chunk * hrow : 0;
     T *const h1 = a.hist + hb, *const h2 = a.hist_mode == 2 ? a.hist2 + hb : nullptr;
@@ -287,9 +290,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
                 T *vp = vel0 + m * a.vel_step;
                 asm volatile("" : "+s"(vp));        // made here: K descriptors kept would spill
                 const auto rv = __builtin_amdgcn_make_buffer_rsrc((void *)vp, 0, bytes, 0x00027000);
-                const int vo = rr >= K && rr < nit - K ? vown : OOB;
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, -inc * a.inv_dt), rv, vo,
-                                                       min(max(ya - K + rr, 0), a.ny - 1) * rowb, 2);
+                const int vo = rr >= K && rr < nit - K ? vown + (ya - K + rr) * rowb : OOB;
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, -inc * a.inv_dt), rv, vo, 0, 2);
             }
             if (m + 1 < K) {
                 L[m + 1 < K ? m + 1 : 0][Q] = out;
@@ -300,9 +302,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         }
         {   // row y - K, one of the chunk's own from iteration 2 K on
             typedef unsigned int U4 __attribute__((ext_vector_type(4)));
-            const int vo = i < 2 * K || i >= nit ? (int)0x80000000 : vown, so = max(y - K, 0) * rowb;
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, last), rop, vo, so, 0);
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, lastc), rom, vo, so, 0);
+            const int vo = i < 2 * K || i >= nit ? OOB : vown + (y - K) * rowb;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, last), rop, vo, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, lastc), rom, vo, 0, 0);
             if constexpr (EXT == 1) {
                 const int64_t hs = max(hm, 0) * hrow;
                 const auto r1 = __builtin_amdgcn_make_buffer_rsrc((void *)(h1 + hs), 0, 0x7ffffff0, 0x00027000);

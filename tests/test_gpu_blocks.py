@@ -105,6 +105,7 @@ def test_jacobian_histories_in_neighbouring_rows(mgrt, L, prec):
 @pytest.mark.parametrize("cfg,N,L,src,steps,prec,level", [
     ("c1", 24, 2, 2, 300, 64, "coarse"), ("c1", 45, 0, 3, 301, 64, "fine"), ("c1", 48, 2, 1, 300, 64, "coarse"),
     ("c1", 96, 3, 23, 300, 32, "coarse"), ("c1", 300, 2, 33, 263, 32, "fine"), ("c1", 300, 2, 9, 263, 64, "coarse"),
+    ("c1", 400, 2, 64, 265, 32, "fine"), ("c1", 400, 2, 32, 263, 64, "coarse"),
     ("c4", 12, 1, 4, 300, 64, "coarse"), ("c4", 24, 1, 3, 270, 32, "coarse"), ("c4", 48, 0, 16, 260, 32, "fine")])
 def test_gradient_with_all_velocities_kept(mgrt, cfg, N, L, src, steps, prec, level):
     """One segment (both sweeps several steps per launch) against checkpointed segments of one
