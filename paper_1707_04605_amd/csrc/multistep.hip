@@ -70,6 +70,10 @@ struct Blocks {
 namespace {
 
 constexpr int BL_FIELD = 32768;   // bytes of a p buffer, at most
+// steps per launch of strips: FP64's coefficient rings of 8 rows leave a SIMD one wave, of 6
+// two (513^2 nodes x 30 columns: 16.2 -> 12.9 us a step)
+template <typename T>
+constexpr int STRIP_K = sizeof(T) == 4 ? 8 : 6;
 constexpr int BL_CAP = 64;        // nodal loads / taps per tile and group (held in LDS)
 // Runs of several columns take one launch per step below this many steps: the regions and
 // their upload cost about as much as 100 one-step launches, once per mesh and shape (first
@@ -716,8 +720,10 @@ Blocks *plan_blocks(Ctx &c, int prec, const StepOp &op, int64_t n_cols, int B, i
             if (vec > 1 && !corr) {
                 if (c.grid_nx < 0) c.grid_nx = grid_row(hm);
                 if (c.grid_nx > 0) {
+                    const int kr = k;
+                    k = esz == 4 ? STRIP_K<float> : STRIP_K<double>;
                     const int64_t strips = (c.grid_nx + 64 - 2 * k - 1) / (64 - 2 * k), ny = n / c.grid_nx;
-                    const int64_t slots = esz == 4 ? 2048 : 1024;    // 57 and 114 KB of LDS per four waves
+                    const int64_t slots = 2048;          // 57 and 74 KB of LDS per four waves
                     double best = 1e300;
                     int64_t chunks = 1;
                     for (int64_t ch = 1; ch <= std::max<int64_t>(1, ny / 4); ++ch) {
@@ -727,7 +733,7 @@ Blocks *plan_blocks(Ctx &c, int prec, const StepOp &op, int64_t n_cols, int B, i
                             chunks = ch;
                         }
                     }
-                    const double us_strips = ((esz == 4 ? 0.82 : 0.92) * best + 6.0) / k;
+                    const double us_strips = ((esz == 4 ? 0.82 : 0.69) * best + 6.0) / k;
                     const double us_regions = (esz == 4 ? 4.5e-6 : 5.5e-6) * n * G + 1.0;
                     if (us_strips < us_regions)
                         return lookup(-vec * esz, G, [&] {
@@ -742,6 +748,7 @@ Blocks *plan_blocks(Ctx &c, int prec, const StepOp &op, int64_t n_cols, int B, i
                             b->n_tiles = strips * chunks;
                             return b;
                         });
+                    k = kr;
                 }
             }
             if (n_cols == 1 ? n >= 2048 : n * G <= 200 * 256) k = 12;
@@ -997,7 +1004,7 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
             else if (run.d_vel_out) go(k_strips<T, VEC, KS, 2>);
             else go(k_strips<T, VEC, KS, 0>);
         };
-        if (ks == 8) by_ext(std::integral_constant<int, 8>{});
+        if (ks == STRIP_K<T>) by_ext(std::integral_constant<int, STRIP_K<T>>{});
         else if (ks == 4) by_ext(std::integral_constant<int, 4>{});
         else if (ks == 2) by_ext(std::integral_constant<int, 2>{});
         else by_ext(std::integral_constant<int, 1>{});

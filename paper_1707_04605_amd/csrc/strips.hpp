@@ -64,10 +64,12 @@ template <typename T, int VEC, int K, int EXT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_strips(
     const StripArgs<T> a) {
     typedef typename GroupVec<T, VEC>::type V;
-    constexpr int R = K <= 1 ? 1 : K <= 2 ? 2 : K <= 4 ? 4 : 8;
+    constexpr int R = K <= 1 ? 1 : K <= 2 ? 2 : K <= 4 ? 4 : K <= 6 ? 6 : 8;
+    // loads of the steps: FP32 in LDS, FP64 in registers (two waves a SIMD leave 20 KB a wave)
+    constexpr bool LDS_ADD = sizeof(T) == 4;
     __shared__ T cf[4][R][5][64];
     __shared__ int32_t hr[EXT == 1 ? 4 : 1][R][64];
-    __shared__ T adds[4][K][BL_CAP], tapv[4][K][BL_CAP];     // loads of the steps, values of the taps
+    __shared__ T adds[LDS_ADD ? 4 : 1][LDS_ADD ? K : 1][BL_CAP], tapv[4][K][BL_CAP];    // tapv: values of the taps
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t l0 = a.done[a.slot];
     if (blockIdx.x == 0 && threadIdx.x == 0) a.done[a.slot ^ 1] = l0 + K;
@@ -115,13 +117,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     auto place = [&](int loc) { return (loc & 63) < sh || loc >> 6 < sh ? -1 : loc - sh * 65; };
     int lloc = -1, lcol = 0, tloc = -1, tcol = 0;
     double lw = 0.0;
+    T add_of[LDS_ADD ? 1 : K] = {};
     if (lane < nl) {
         lloc = place(a.ld_loc[lb + lane]);
         lcol = a.ld_col[lb + lane];
         const double w = a.ld_w[lb + lane];
         const double *ser = a.series + (int64_t)a.ld_sid[lb + lane] * a.series_len + a.step0 + l0;
 #pragma unroll
-        for (int m = 0; m < K; ++m) load_value(w, ser[m], adds[wave][m][lane]);
+        for (int m = 0; m < K; ++m) load_value(w, ser[m], LDS_ADD ? adds[wave][m][lane] : add_of[LDS_ADD ? 0 : m]);
         lw = w;
     }
     if (lane < nq) {
@@ -209,7 +212,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         T cv[2][5];
         auto coef = [&](int m) {
 #pragma unroll
-            for (int q = 0; q < 5; ++q) cv[m & 1][q] = cf[wave][(i - 1 - m) & (R - 1)][q][lane];
+            for (int q = 0; q < 5; ++q) cv[m & 1][q] = cf[wave][(uint32_t)(i - 1 - m) % R][q][lane];
         };
         coef(0);
 #pragma unroll
@@ -217,7 +220,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             // row r = y - 1 - m, step m + 1; the first rows of a chunk are still incomplete
             if (i < 2 * m + 2) break;
             const int rr = i - 1 - m;
-            [[maybe_unused]] const int slot = rr & (R - 1);
+            [[maybe_unused]] const int slot = (uint32_t)rr % R;
             if (m + 1 < K) coef(m + 1);
             __builtin_amdgcn_sched_barrier(0);
             const V c = L[m][QP], dn = L[m][QO], up = L[m][Q];
@@ -249,7 +252,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             if (lrows & (1u << m)) {
                 for (uint64_t b = __ballot(lloc >> 6 == rr); b; b &= b - 1) {
                     const int e = __ffsll((unsigned long long)b) - 1;
-                    const T add = adds[wave][m][e];
+                    T add;
+                    if constexpr (LDS_ADD) add = adds[wave][m][e];
+                    else add = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(add_of[m]), e),
+                                                __builtin_amdgcn_readlane(__double2loint(add_of[m]), e));
                     const double w = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(lw), e),
                                                       __builtin_amdgcn_readlane(__double2loint(lw), e));
                     const int at = __builtin_amdgcn_readlane(lloc, e) & 63, col = __builtin_amdgcn_readlane(lcol, e);
@@ -315,12 +321,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         }
         // row y's coefficients: first used by the next iteration
 #pragma unroll
-        for (int q = 0; q < 5; ++q) cf[wave][i & (R - 1)][q][lane] = cw[q];
+        for (int q = 0; q < 5; ++q) cf[wave][(uint32_t)i % R][q][lane] = cw[q];
         m1 = m1n;
         lrows = lrows << 1 | (uint32_t)(__ballot(lloc >> 6 == i) != 0);
         trows = trows << 1 | (uint32_t)(__ballot(tloc >> 6 == i) != 0);
         if constexpr (EXT == 1) {
-            hr[wave][i & (R - 1)][lane] = hw;
+            hr[wave][(uint32_t)i % R][lane] = hw;
             hrows = hrows << 1 | (uint32_t)(__ballot(hw >= 0) != 0);
         }
     };

@@ -29,11 +29,11 @@ def _both(ctx, p, rec, prec):
 
 
 # one tile (2D up to 2,048 nodes, 3D up to 4,096), regions with one column a group (k = 12)
-# and four or two, strips (k = 8) with 7 steps left over, 3D regions (k = 4)
+# and four or two, strips (k = 8, FP64 6) with 7 or 5 steps left over, 3D regions (k = 4)
 @pytest.mark.parametrize("cfg,N,src,steps,prec,k", [
     ("c1", 24, 2, 257, 64, 64), ("c1", 44, 5, 320, 32, 64), ("c1", 45, 3, 300, 32, 12),
     ("c1", 45, 3, 301, 64, 12), ("c1", 96, 23, 300, 32, 8), ("c1", 150, 15, 263, 64, 8),
-    ("c1", 300, 33, 303, 32, 8), ("c1", 300, 31, 263, 64, 8), ("c1", 301, 64, 258, 32, 8),
+    ("c1", 300, 33, 303, 32, 8), ("c1", 300, 31, 263, 64, 6), ("c1", 301, 64, 258, 32, 8),
     ("c4", 12, 4, 300, 64, 64), ("c4", 16, 5, 257, 32, 4), ("c4", 24, 3, 300, 32, 4)])
 def test_several_columns_equal_one_step(mgrt, cfg, N, src, steps, prec, k):
     p = configs.make(cfg, N=N, L=0, n_src=src, n_steps=steps)
@@ -94,7 +94,7 @@ def test_jacobian_histories_in_neighbouring_rows(mgrt, L, prec):
     kw = dict(mode="mg", precision=prec)
     a = ctx.jacobian_coarse(p.src, p.rec, p.wavelet, p.dt, p.n_steps, p.sample_steps, **kw)
     t = ctx.last_timing()
-    assert t["steps_per_launch"] == 8
+    assert t["steps_per_launch"] == (8 if prec == 32 else 6)
     b = ctx.jacobian_coarse(p.src, p.rec, p.wavelet, p.dt, p.n_steps, p.sample_steps, batch=t["batch"], **kw)
     assert ctx.last_timing()["steps_per_launch"] == 1
     assert np.array_equal(a, b)
