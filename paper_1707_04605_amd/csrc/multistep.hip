@@ -75,9 +75,8 @@ constexpr int BL_FIELD = 32768;   // bytes of a p buffer, at most
 template <typename T>
 constexpr int STRIP_K = sizeof(T) == 4 ? 8 : 6;
 constexpr int BL_CAP = 64;        // nodal loads / taps per tile and group (held in LDS)
-// Runs of several columns take one launch per step below this many steps: the regions and
-// their upload cost about as much as 100 one-step launches, once per mesh and shape (first
-// call on 33^2 nodes, 3 columns, FP64, 200 steps: 1.6 ms with and 1.1 ms without).
+// Runs of several columns take one launch per step below this many steps: building the
+// regions costs about as much as a hundred one-step launches, once per mesh and shape.
 constexpr int64_t BL_MIN_STEPS = 256;
 
 template <typename T, int VEC>
@@ -420,7 +419,7 @@ void launch_blocks_x(const BlockArgs<T> &a, BlockLaunch &L) {
     else go(k_blocks<T, VEC, W, NPT, false>);
 }
 
-// Entries per thread that the kernel's registers allow (16 KB of VGPRs per 1,024 lanes)
+// Entries per thread that the kernel's registers allow without spills
 template <typename T, int VEC>
 constexpr int max_npt(int W) {
     return W == 4 ? 4 : W == 6 ? (VEC == 1 || sizeof(T) == 4 ? 4 : 2) : W == 8 ? 2 : 1;

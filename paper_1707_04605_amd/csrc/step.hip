@@ -42,6 +42,7 @@
 
 #include "mgrt_internal.hpp"
 #include "step_kernels.hpp"
+#include "step_pml.hpp"
 
 namespace mgrt {
 
@@ -590,6 +591,7 @@ void run_batch_t(Ctx &c, StepOp &op, BatchRun &run) {
     const PmlOp &P = op.pml;
     DevBuf q0, q1;
     T *q0p = nullptr, *q1p = nullptr;
+    PmlArgs<T> pa{};
     const size_t qbytes = (size_t)P.n_ent * run.B * sizeof(T);
     if (P.n_ent > 0) {
         if (run.arena) {
@@ -608,13 +610,13 @@ void run_batch_t(Ctx &c, StepOp &op, BatchRun &run) {
             q1.alloc(qbytes);
             q1p = q1.as<T>();
         }
-        a.pml_ptr = P.row_ptr.as<int32_t>();
-        a.pml_ent = P.row_ent.as<int32_t>();
-        a.pml_coef = P.row_coef.as<T>();
-        a.pml_rec = P.ent_rec.as<uint32_t>();
-        a.pml_n_ent = P.n_ent;
-        a.pml_nv = c.hm.d + 1;
-        a.pml_blocks = (int32_t)(((P.n_ent + S - 1) / S + 7) / 8 * 8);     // S = entries a workgroup
+        pa.ptr = P.row_ptr.as<int32_t>();
+        pa.ent = P.row_ent.as<int32_t>();
+        pa.coef = P.row_coef.as<T>();
+        pa.rec = P.ent_rec.as<uint32_t>();
+        pa.n_ent = P.n_ent;
+        pa.nv = c.hm.d + 1;
+        pa.blocks = (int32_t)(((P.n_ent + S - 1) / S + 7) / 8 * 8);     // S = entries a workgroup
     }
     T *qa = run.d_q ? static_cast<T *>(run.d_q) : q0p, *qb_ = q1p;
     T *bufA = static_cast<T *>(run.d_p);
@@ -642,11 +644,13 @@ void run_batch_t(Ctx &c, StepOp &op, BatchRun &run) {
         }
         if (P.n_ent > 0) {
             // the step reads q_{l-1/2} (qa) for its load; the update writes q_{l+1/2} (qb_)
-            a.pml_q = qa;
-            a.pml_qn = qb_;
+            pa.q = qa;
+            pa.qn = qb_;
+            launch_step_pml<T>(a, pa, run.B, W, nt, grid, s);
+            std::swap(qa, qb_);
+        } else {
+            launch_step<T>(a, run.B, W, nt, pk, grid, s);
         }
-        launch_step<T>(a, run.B, W, nt, pk, grid + a.pml_blocks, s);
-        if (P.n_ent > 0) std::swap(qa, qb_);
         if (flush) {
             hipLaunchKernelGGL(k_hist_flush<T>, dim3((hist_nser + 63) / 64), dim3(256), 0, s,
                                static_cast<const T *>(hist_stage), hist_nser, (int)(slot + 1),
