@@ -4,7 +4,7 @@
 //
 // The update needs p_l and q_{l-1/2} alone, as the step does, and takes workgroups of the
 // same launch.  Launches that short are bound by their latency: two of them took 10.7 us a
-// step (321^2 nodes x 16 columns FP32), one takes 7.6; 1,001^2 x 32 100 and 88 us.
+// step (321^2 nodes x 16 columns FP32), one takes 7.8; 1,001^2 x 32 100 and 98 us.
 #pragma once
 
 #include "step_kernels.hpp"
