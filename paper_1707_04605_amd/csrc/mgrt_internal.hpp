@@ -296,8 +296,9 @@ struct Ctx {
     std::map<std::tuple<int, int>, std::unique_ptr<StepOp>> ops;   // key (S, prec)
     std::map<std::tuple<int, int, int, int>, Tuned> tuned;         // (prec, B, S, W) -> variant
     std::map<std::tuple<int, int64_t>, int> batch_tuned;           // (prec, columns) -> B
-    // (bytes per entry and field, tiles asked for, steps) -> regions; dropped with the mesh
-    std::map<std::tuple<int, int64_t, int>, std::shared_ptr<Blocks>> blocks;
+    // (strips, precision, columns a group, padded row width, tiles asked for or (strips) groups,
+    // steps a launch) -> regions or strips; dropped with the mesh
+    std::map<std::tuple<bool, int, int, int, int64_t, int>, std::shared_ptr<Blocks>> blocks;
     int64_t grid_nx = -1;              // row length of a lexicographic 2D grid, 0: none, -1: not looked at
     std::shared_ptr<void> fft_plans;   // deconv.hip: FFT plans kept per (length, batch, precision)
     mgrt_timing timing{};

@@ -699,8 +699,10 @@ Blocks *plan_blocks(Ctx &c, int prec, const StepOp &op, int64_t n_cols, int B, i
     int vec = n * n_cols <= 131072 || B == 1 ? 1 : 16 / esz;
     int k = 8;
     int64_t tiles = 1, G = 0;
-    auto lookup = [&](int kind, int64_t a, auto &&build) -> Blocks * {
-        const auto key = std::make_tuple(kind, a, k);
+    // tables hold columns in groups of vec and entries of vec * esz bytes: FP32 in fours and FP64
+    // in pairs have the same bytes and are not the same tables
+    auto lookup = [&](bool strip, int64_t a, auto &&build) -> Blocks * {
+        const auto key = std::make_tuple(strip, prec, vec, W, a, k);
         auto it = c.blocks.find(key);
         if (it == c.blocks.end()) it = c.blocks.emplace(key, build()).first;
         return it->second->k ? it->second.get() : nullptr;
@@ -735,7 +737,7 @@ Blocks *plan_blocks(Ctx &c, int prec, const StepOp &op, int64_t n_cols, int B, i
                     const double us_strips = ((esz == 4 ? 0.82 : 0.69) * best + 6.0) / k;
                     const double us_regions = (esz == 4 ? 4.5e-6 : 5.5e-6) * n * G + 1.0;
                     if (us_strips < us_regions)
-                        return lookup(-vec * esz, G, [&] {
+                        return lookup(true, G, [&] {
                             auto b = std::make_shared<Blocks>();
                             b->k = k;
                             b->W = W;
@@ -761,7 +763,7 @@ Blocks *plan_blocks(Ctx &c, int prec, const StepOp &op, int64_t n_cols, int B, i
         while (region_estimate(hm.d, s, k) > cap && s > 1) s *= 0.98;
         tiles = std::max<int64_t>(1, (int64_t)std::ceil(n / s));
     }
-    return lookup(vec * esz, tiles, [&] {
+    return lookup(false, tiles, [&] {
         std::shared_ptr<Blocks> b;
         int64_t tl = tiles;
         for (int tries = 0; tries < 8 && !b && n / tl >= 4; ++tries) {
@@ -829,6 +831,9 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
     const int64_t n = c.hm.n;
     hipStream_t s = c.stream;
     const int64_t groups = live_groups(run, B.vec);
+    // the kernels take 16 bytes of columns or one; the caller's fields hold run.B columns
+    MGRT_REQUIRE((B.vec == 1 || B.vec == 16 / (int)sizeof(T)) && groups * B.vec <= run.B, MGRT_E_STATE,
+                 "regions of another precision or batch width");
     GroupLists ld = group_lists(B, groups, run.inj, c.hm.iperm, false, [](const Injection &e) { return e.sid; });
     GroupLists tp = group_lists(B, groups, run.rec, c.hm.iperm, true, [](const Record &e) { return e.dst; });
     // strips record histories (at 31-bit offsets) or the velocity field, not both
