@@ -63,6 +63,9 @@ constexpr int CORR_R = 4;     // outputs per thread per pass (256 * 4 sample ste
 constexpr int CORR_CH = 512;  // impulse-response samples a half of the workgroup takes in turn
 constexpr int CORR_U = 16;    // of them held at a time
 
+__device__ __forceinline__ uint32_t high_word(float x) { return (uint32_t)__float_as_int(x); }
+__device__ __forceinline__ uint32_t high_word(double x) { return (uint32_t)__double2hiint(x); }
+
 // C[(pair)*K + k][c] = sum_{u=0}^{l_k} lam[c][q][u] * b[c][fcol][l_k - u]
 // One workgroup per (coarse node, receiver column).  The forward velocity series b sits
 // in LDS for the whole kernel (in its own precision) behind CORR_U zeros; output k of a lane
@@ -121,16 +124,30 @@ __global__ __launch_bounds__(512) void k_corr(const T *__restrict__ bh, const T 
                     for (int e = 0; e < CORR_U; ++e) raw[e] = u0 + e < N ? lser[u0 + e] : T(0);
                 }
                 double lam[CORR_U];
+                uint32_t mag = 0;               // the largest exponent of the chunk
 #pragma unroll
-                for (int e = 0; e < CORR_U; ++e) lam[e] = (double)raw[e];
+                for (int e = 0; e < CORR_U; ++e) {
+                    lam[e] = (double)raw[e];
+                    mag = std::max(mag, high_word(raw[e]) & 0x7fffffffu);
+                }
+                // scalar work beside the products: a sum that has ended reads zeros, and zero times a
+                // value that is not finite would not leave it alone
+                const bool finite = mag < (sizeof(T) == 4 ? 0x7f800000u : 0x7ff00000u);
 #pragma unroll
                 for (int r = 0; r < CORR_R; ++r) {
                     if (u0 > top[r]) continue;
-                    // sums that have ended read zeros
-                    const T *bp = bl + std::max(lr[r] - u0, -1);     // b[l - u0 - e] = bp[-e]
+                    const int left = std::max(lr[r] - u0, -1);
+                    const T *bp = bl + left;                         // b[l - u0 - e] = bp[-e]
                     double a = acc[r];
+                    if (finite) {
 #pragma unroll
-                    for (int e = 0; e < CORR_U; ++e) a = fma(lam[e], (double)bp[-e], a);
+                        for (int e = 0; e < CORR_U; ++e) a = fma(lam[e], (double)bp[-e], a);
+                    } else {
+                        for (int e = 0; e < CORR_U; ++e) {
+                            const double x = u0 + e < N ? (double)lser[u0 + e] : 0.0;
+                            if (e <= left) a = fma(x, (double)bp[-e], a);
+                        }
+                    }
                     acc[r] = a;
                 }
             }
