@@ -26,7 +26,8 @@
  *     says "device" or opts->flags has MGRT_F_DEVICE_OUT for outputs.  The library
  *     copies what it keeps into device memory it owns and frees in mgrt_destroy().
  *     Device blocks that a call frees wait for later calls of any context, up to 16 GiB
- *     per device, until the device's last context is destroyed.
+ *     per device (and the mem_budget_gb of a call that has one), until a context of the
+ *     device is destroyed or mgrt_release_cached() gives them back.
  *   - Calls are synchronous with respect to the host: on return, outputs are written.
  *   - A context is not thread-safe; separate contexts are independent.
  *   - All floating-point inputs are FP64; "precision" selects the arithmetic of the
@@ -88,7 +89,8 @@ typedef struct {
     int batch;                 /* sources per launch (1..128, power of two), 0 = auto   */
                                /* (timed by the batch tuner on large meshes)           */
     int flags;                 /* MGRT_F_*                                               */
-    double mem_budget_gb;      /* device memory the call may plan for; 0 = free memory  */
+    double mem_budget_gb;      /* device memory the call may plan for and leave waiting */
+                               /* for later calls; 0 = free memory                      */
     double deconv_delta;       /* MGRT_JAC_DECONV: Tikhonov parameter, relative to the   */
                                /* peak power max|F|^2 of the source function (>= 0)      */
     int launch;                /* batched stepping launch variant: 0 = the tuned one    */
@@ -142,6 +144,10 @@ typedef struct {
  * on (the caller keeps it alive) or NULL for a stream the context owns. */
 int mgrt_create(int device, void *hip_stream, mgrt_ctx **out);
 int mgrt_destroy(mgrt_ctx *ctx);
+/* Free the device blocks that wait on ctx's device for later calls (for another allocator in
+ * the process, or another process).  A block may be up to an eighth larger than what it is
+ * used for; what a call holds while it runs stays. */
+int mgrt_release_cached(mgrt_ctx *ctx);
 /* Message of the last failing call on ctx (static storage of the context). */
 const char *mgrt_last_error(const mgrt_ctx *ctx);
 

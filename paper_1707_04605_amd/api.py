@@ -79,6 +79,10 @@ class Context:
             self.lib.mgrt_destroy(self._h)
             self._h = C.c_void_p()
 
+    def release_cached(self):
+        """mgrt_release_cached: free the device blocks that wait for later calls."""
+        self._check(self.lib.mgrt_release_cached(self._h), "mgrt_release_cached")
+
     def __del__(self):
         try:
             self.close()

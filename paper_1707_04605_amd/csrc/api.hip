@@ -10,10 +10,11 @@
 namespace mgrt {
 
 // ------------------------------------------------------------------------------------
-// Device blocks between calls.  Bounded (CACHE_BYTES per device), shared by all contexts of
-// a device under a mutex, drained when an allocation fails and when the device's last
-// context is destroyed.  A block enters only after the device is idle, as hipFree would
-// wait, so that no kernel of another stream still uses it.
+// Device blocks between calls.  Bounded (CACHE_BYTES per device, and the memory budget of a call
+// that has one), shared by all contexts of a device under a mutex, given back on request, when an
+// allocation fails and when a context of the device is destroyed.  A block enters only after
+// the device is idle, as hipFree would wait, so that no kernel of another stream still uses it.
+// Nothing here throws: blocks are given and taken in destructors and at the C entries.
 namespace {
 
 constexpr size_t CACHE_MIN = 1 << 20;             // smaller blocks: hipMalloc takes about 1 us
@@ -28,15 +29,15 @@ struct BlockCache {
 
 // never destroyed: contexts may outlive static objects, the runtime may not
 BlockCache *block_cache() {
-    static BlockCache *all = new BlockCache[CACHE_DEVICES];
+    static BlockCache *all = new (std::nothrow) BlockCache[CACHE_DEVICES];
     int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= CACHE_DEVICES) return nullptr;
+    if (!all || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= CACHE_DEVICES) return nullptr;
     return all + dev;
 }
 
 }  // namespace
 
-void *cache_take(size_t bytes, size_t *got) {
+void *cache_take(size_t bytes, size_t *got) noexcept {
     BlockCache *c = bytes >= CACHE_MIN ? block_cache() : nullptr;
     if (!c) return nullptr;
     std::lock_guard<std::mutex> lk(c->mu);
@@ -53,59 +54,58 @@ void *cache_take(size_t bytes, size_t *got) {
     return p;
 }
 
-bool cache_give(void *p, size_t bytes, int device) {
+bool cache_give(void *p, size_t bytes, int device) noexcept {
     int cur = -1;
     if (bytes < CACHE_MIN || bytes > CACHE_BYTES || hipGetDevice(&cur) != hipSuccess || cur != device) return false;
     BlockCache *c = block_cache();
     if (!c || hipDeviceSynchronize() != hipSuccess) return false;
-    std::vector<void *> out;
-    {
-        std::lock_guard<std::mutex> lk(c->mu);
-        if (c->contexts == 0) return false;
-        size_t k = 0;
-        while (c->bytes + bytes > CACHE_BYTES) {      // the oldest make room
-            c->bytes -= c->blocks[k].first;
-            out.push_back(c->blocks[k++].second);
-        }
-        c->blocks.erase(c->blocks.begin(), c->blocks.begin() + k);
+    (void)cache_trim(CACHE_BYTES - bytes);            // the oldest make room
+    std::lock_guard<std::mutex> lk(c->mu);
+    if (c->contexts == 0 || c->bytes + bytes > CACHE_BYTES) return false;
+    try {
         c->blocks.emplace_back(bytes, p);
-        c->bytes += bytes;
+    } catch (const std::bad_alloc &) {
+        return false;
     }
-    for (void *q : out) (void)hipFree(q);
+    c->bytes += bytes;
     return true;
 }
 
-bool cache_drain() {
+bool cache_trim(size_t keep) noexcept {
     BlockCache *c = block_cache();
     if (!c) return false;
-    std::vector<std::pair<size_t, void *>> out;
-    {
-        std::lock_guard<std::mutex> lk(c->mu);
-        out.swap(c->blocks);
-        c->bytes = 0;
+    bool any = false;
+    for (;;) {
+        void *p = nullptr;
+        {
+            std::lock_guard<std::mutex> lk(c->mu);
+            if (c->bytes <= keep || c->blocks.empty()) return any;
+            p = c->blocks.front().second;
+            c->bytes -= c->blocks.front().first;
+            c->blocks.erase(c->blocks.begin());
+        }
+        (void)hipFree(p);
+        any = true;
     }
-    for (auto &b : out) (void)hipFree(b.second);
-    return !out.empty();
 }
 
-size_t cache_bytes() {
+size_t cache_bytes() noexcept {
     BlockCache *c = block_cache();
     if (!c) return 0;
     std::lock_guard<std::mutex> lk(c->mu);
     return c->bytes;
 }
 
-// A context enters (+1) or leaves (-1) the current device; the last one drains the cache.
-static void cache_contexts(int add) {
+// A context enters (+1) or leaves (-1) the current device; one that leaves takes the blocks
+// that wait along.
+static void cache_contexts(int add) noexcept {
     BlockCache *c = block_cache();
     if (!c) return;
-    bool last = false;
     {
         std::lock_guard<std::mutex> lk(c->mu);
         c->contexts += add;
-        last = c->contexts == 0;
     }
-    if (last) (void)cache_drain();
+    if (add < 0) (void)cache_trim(0);
 }
 
 int run_precision(const mgrt_run_opts *o) {
@@ -446,6 +446,10 @@ int mgrt_destroy(mgrt_ctx *ctx) {
     cache_contexts(-1);
     if (own) (void)hipStreamDestroy(s);
     return MGRT_OK;
+}
+
+int mgrt_release_cached(mgrt_ctx *ctx) {
+    return mgrt_guarded(ctx, [&](Ctx &) { (void)cache_trim(0); });
 }
 
 const char *mgrt_last_error(const mgrt_ctx *ctx) {

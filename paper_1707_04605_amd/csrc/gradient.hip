@@ -257,6 +257,7 @@ extern "C" int mgrt_misfit_gradient(mgrt_ctx *ctx, int64_t n_src, const double *
         MGRT_REQUIRE(level == 1 || c.hm.nc > 0, MGRT_E_STATE, "no coarse level uploaded");
         MGRT_REQUIRE(!(opts && (opts->flags & MGRT_F_DEVICE_OUT)), MGRT_E_ARG,
                      "gradient output is a host array");
+        const CacheBudget budget(opts);
         const int flags = opts ? opts->flags : 0;
         const int prec = run_precision(opts);
         Acquisition aq = make_acquisition(c, n_src, src_xyz, n_rec, rec_xyz);

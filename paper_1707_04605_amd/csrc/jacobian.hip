@@ -613,6 +613,7 @@ extern "C" int mgrt_jacobian_coarse(mgrt_ctx *ctx, int64_t n_src, const double *
             MGRT_REQUIRE(ss[k] >= 0 && ss[k] < n_steps, MGRT_E_ARG, "sample step out of range");
             if (k) MGRT_REQUIRE(ss[k] > ss[k - 1], MGRT_E_ARG, "sample steps must increase");
         }
+        const CacheBudget budget(opts);
         const int flags = opts ? opts->flags : 0;
         const int prec = run_precision(opts);
         Acquisition aq = make_acquisition(c, n_src, src_xyz, n_rec, rec_xyz);

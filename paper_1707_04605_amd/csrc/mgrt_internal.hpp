@@ -40,12 +40,12 @@ struct Error : std::runtime_error {
 // allocation of about their size: once a process has allocated and freed about the device's
 // memory, the driver wipes what is freed, and hipFree takes 30 ms per GB (4.5 GB: 0.7 ms
 // before, 135 ms after).  cache_take returns a block of at least `bytes`, or null; cache_give
-// takes a block of `device` or declines it; cache_drain frees what waits on the current device (and says
-// whether anything did); cache_bytes is how much that is.
-void *cache_take(size_t bytes, size_t *got);
-bool cache_give(void *p, size_t bytes, int device);
-bool cache_drain();
-size_t cache_bytes();
+// takes a block of `device` or declines it; cache_trim frees the oldest that wait on the current
+// device until at most `keep` bytes do (and says whether any went); cache_bytes is how much waits.
+void *cache_take(size_t bytes, size_t *got) noexcept;
+bool cache_give(void *p, size_t bytes, int device) noexcept;
+bool cache_trim(size_t keep) noexcept;
+size_t cache_bytes() noexcept;
 constexpr size_t CACHE_BYTES = 16ull << 30;      // per device
 
 // Free and total bytes of the current device; cached blocks count as free.
@@ -54,6 +54,21 @@ inline void device_memory(size_t *fr, size_t *tot) {
     if (e != hipSuccess) throw Error(MGRT_E_HIP, std::string("hipMemGetInfo: ") + hipGetErrorString(e));
     *fr += cache_bytes();
 }
+
+// A call with a memory budget leaves no more than that waiting.  Declared before the call's
+// buffers, which are freed (into the cache) first.
+struct CacheBudget {
+    size_t keep;
+    explicit CacheBudget(const mgrt_run_opts *o)
+        : keep(o && o->mem_budget_gb > 0
+                   ? (size_t)std::min((double)CACHE_BYTES, o->mem_budget_gb * (double)(1ull << 30))
+                   : CACHE_BYTES) {
+        (void)cache_trim(keep);
+    }
+    CacheBudget(const CacheBudget &) = delete;
+    CacheBudget &operator=(const CacheBudget &) = delete;
+    ~CacheBudget() { (void)cache_trim(keep); }
+};
 
 // Owning device allocation.
 struct DevBuf {
@@ -83,7 +98,7 @@ struct DevBuf {
         p = cache_take(b, &held);
         if (!p) {
             hipError_t e = hipMalloc(&p, b);
-            if (e != hipSuccess && cache_drain()) {
+            if (e != hipSuccess && cache_trim(0)) {
                 (void)hipGetLastError();
                 e = hipMalloc(&p, b);
             }

@@ -83,6 +83,7 @@ def load() -> C.CDLL:
     lib = C.CDLL(LIB_PATH)
     lib.mgrt_create.argtypes = [C.c_int, vp, C.POINTER(vp)]
     lib.mgrt_destroy.argtypes = [vp]
+    lib.mgrt_release_cached.argtypes = [vp]
     lib.mgrt_last_error.argtypes = [vp]
     lib.mgrt_last_error.restype = C.c_char_p
     lib.mgrt_upload_mesh.argtypes = [vp, C.c_int, i64, vp, i64, vp, i64, vp, vp, i64, vp, vp]
