@@ -81,10 +81,23 @@ void make_plans(FftPlan &fwd, FftPlan &inv, int L, int64_t batch, hipStream_t s)
     const int NF = L / 2 + 1, LP = 2 * NF;
     int n[1] = {L}, nr[1] = {LP}, nc[1] = {NF};
     const bool dbl = sizeof(T) == 8;
-    MGRT_FFT(hipfftPlanMany(&fwd.h, 1, n, nr, 1, LP, nc, 1, NF, dbl ? HIPFFT_D2Z : HIPFFT_R2C, (int)batch));
-    fwd.live = true;
-    MGRT_FFT(hipfftPlanMany(&inv.h, 1, n, nc, 1, NF, nr, 1, LP, dbl ? HIPFFT_Z2D : HIPFFT_C2R, (int)batch));
-    inv.live = true;
+    // the library allocates the plan's work area itself: when that fails, the blocks that wait
+    // for later calls (which count as free memory) make room
+    auto plan = [](FftPlan &p, auto &&make) {
+        hipfftResult r = make(&p.h);
+        if (r != HIPFFT_SUCCESS && cache_trim(0)) {
+            (void)hipGetLastError();
+            r = make(&p.h);
+        }
+        MGRT_FFT(r);
+        p.live = true;
+    };
+    plan(fwd, [&](hipfftHandle *h) {
+        return hipfftPlanMany(h, 1, n, nr, 1, LP, nc, 1, NF, dbl ? HIPFFT_D2Z : HIPFFT_R2C, (int)batch);
+    });
+    plan(inv, [&](hipfftHandle *h) {
+        return hipfftPlanMany(h, 1, n, nc, 1, NF, nr, 1, LP, dbl ? HIPFFT_Z2D : HIPFFT_C2R, (int)batch);
+    });
     MGRT_FFT(hipfftSetStream(fwd.h, s));
     MGRT_FFT(hipfftSetStream(inv.h, s));
 }
