@@ -559,6 +559,10 @@ int mgrt_upload_pml(mgrt_ctx *ctx, const double *xi, const double *zeta) {
                      "xi and zeta must both be given or both be null");
         const HostMesh &hm = c.hm;
         const int d = hm.d, V = d + 1;
+        if (c.have_pml != (xi != nullptr)) {      // variants and widths were timed with another step
+            c.tuned.clear();
+            c.batch_tuned.clear();
+        }
         c.have_pml = false;
         c.rxi.clear();
         c.pml_zeta.clear();

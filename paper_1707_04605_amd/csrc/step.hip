@@ -42,7 +42,6 @@
 
 #include "mgrt_internal.hpp"
 #include "step_kernels.hpp"
-#include "step_pml.hpp"
 
 namespace mgrt {
 
@@ -383,18 +382,37 @@ __global__ void k_fill_pattern(T *__restrict__ x, int64_t count, uint32_t salt) 
     x[i] = (T)((double)(h & 0xffffu) * (1.0 / 65536.0) - 0.5);
 }
 
+// The split-field PML's part of the step arguments, but its state (none: pml_blocks stays 0).
+template <typename T>
+void set_pml(StepArgs<T> &a, const Ctx &c, const StepOp &op) {
+    const PmlOp &P = op.pml;
+    if (P.n_ent == 0) return;
+    a.pml_ptr = P.row_ptr.as<int32_t>();
+    a.pml_ent = P.row_ent.as<int32_t>();
+    a.pml_coef = P.row_coef.as<T>();
+    a.pml_rec = P.ent_rec.as<uint32_t>();
+    a.pml_n_ent = P.n_ent;
+    a.pml_nv = c.hm.d + 1;
+    a.pml_blocks = (int32_t)(((P.n_ent + op.S - 1) / op.S + 7) / 8 * 8);     // S = entries a workgroup
+}
+
 // Time every variant on scratch state (pattern-filled fields, no loads or taps: the cost
 // is the memory traffic of the step), two interleaved rounds of a few launches each, and
 // return the variant with the fastest round and the per-launch times.
 template <typename T>
 Tuned tune_variant(Ctx &c, const StepOp &op, const StepArgs<T> &proto, int B, int W, int64_t grid) {
     const size_t slab = (size_t)proto.n * proto.B * sizeof(T);
-    DevBuf sa(slab), sb(slab);
-    const int64_t cnt = proto.n * proto.B;
-    hipLaunchKernelGGL(k_fill_pattern<T>, dim3((cnt + 255) / 256), dim3(256), 0, c.stream,
-                       static_cast<T *>(sa.p), cnt, 0x9e3779b9u);
-    hipLaunchKernelGGL(k_fill_pattern<T>, dim3((cnt + 255) / 256), dim3(256), 0, c.stream,
-                       static_cast<T *>(sb.p), cnt, 0x7f4a7c15u);
+    const int64_t cnt = proto.n * proto.B, qcnt = op.pml.n_ent * proto.B;
+    DevBuf sa(slab), sb(slab), qa((size_t)qcnt * sizeof(T)), qb((size_t)qcnt * sizeof(T));
+    auto fill = [&](DevBuf &b, int64_t n, uint32_t salt) {
+        if (n > 0)
+            hipLaunchKernelGGL(k_fill_pattern<T>, dim3((n + 255) / 256), dim3(256), 0, c.stream,
+                               static_cast<T *>(b.p), n, salt);
+    };
+    fill(sa, cnt, 0x9e3779b9u);
+    fill(sb, cnt, 0x7f4a7c15u);
+    fill(qa, qcnt, 0x85ebca6bu);
+    fill(qb, qcnt, 0xc2b2ae35u);
     MGRT_HIP(hipGetLastError());
     StepArgs<T> a = proto;
     a.parts = nullptr;
@@ -411,7 +429,10 @@ Tuned tune_variant(Ctx &c, const StepOp &op, const StepArgs<T> &proto, int B, in
     // enough launches per round that a round of a small problem lasts well above the
     // timer's resolution
     const int64_t nb = proto.n * proto.B;
-    const int reps = nb > (1 << 22) ? 12 : (int)std::min<int64_t>(200, std::max<int64_t>(24, (1 << 22) / nb));
+    int reps = nb > (1 << 22) ? 12 : (int)std::min<int64_t>(200, std::max<int64_t>(24, (1 << 22) / nb));
+    // a launch with a layer takes up to twice as long: half as many (the first call of 321^2 nodes x
+    // 16 columns, three widths timed: 30.6 -> 24.2 ms)
+    if (op.pml.n_ent > 0) reps /= 2;
     for (int round = 0; round < 2; ++round) {
         for (int v = 0; v < nv; ++v) {
             if (!variant_distinct(v, op)) continue;
@@ -420,7 +441,9 @@ Tuned tune_variant(Ctx &c, const StepOp &op, const StepArgs<T> &proto, int B, in
                 if (r == 2) MGRT_HIP(hipEventRecord(e0, c.stream));
                 a.p = static_cast<T *>(r & 1 ? sb.p : sa.p);
                 a.pm = static_cast<T *>(r & 1 ? sa.p : sb.p);
-                launch_step<T>(a, B, W, v & 1, pk_mode(v, op), grid, c.stream);
+                a.pml_q = static_cast<T *>(r & 1 ? qb.p : qa.p);
+                a.pml_qn = static_cast<T *>(r & 1 ? qa.p : qb.p);
+                launch_step<T>(a, B, W, v & 1, pk_mode(v, op), grid + a.pml_blocks, c.stream);
             }
             MGRT_HIP(hipEventRecord(e1, c.stream));
             MGRT_HIP(hipEventSynchronize(e1));
@@ -456,6 +479,7 @@ StepArgs<T> op_args(const Ctx &c, const StepOp &op, int B) {
     a.per_xcd = (op.n_tiles + 7) / 8;
     a.inv_dt = (T)(1.0 / op.dt);
     for (int k = 0; k < 8; ++k) a.spec_off[k] = op.spec_off[k];
+    set_pml(a, c, op);
     return a;
 }
 
@@ -589,9 +613,9 @@ void run_batch_t(Ctx &c, StepOp &op, BatchRun &run) {
     // split-field PML state of this run: q^(k) of the listed element-directions (zero at
     // the start), ping-pong, and the per-step load rows
     const PmlOp &P = op.pml;
+    set_pml(a, c, op);
     DevBuf q0, q1;
     T *q0p = nullptr, *q1p = nullptr;
-    PmlArgs<T> pa{};
     const size_t qbytes = (size_t)P.n_ent * run.B * sizeof(T);
     if (P.n_ent > 0) {
         if (run.arena) {
@@ -610,13 +634,6 @@ void run_batch_t(Ctx &c, StepOp &op, BatchRun &run) {
             q1.alloc(qbytes);
             q1p = q1.as<T>();
         }
-        pa.ptr = P.row_ptr.as<int32_t>();
-        pa.ent = P.row_ent.as<int32_t>();
-        pa.coef = P.row_coef.as<T>();
-        pa.rec = P.ent_rec.as<uint32_t>();
-        pa.n_ent = P.n_ent;
-        pa.nv = c.hm.d + 1;
-        pa.blocks = (int32_t)(((P.n_ent + S - 1) / S + 7) / 8 * 8);     // S = entries a workgroup
     }
     T *qa = run.d_q ? static_cast<T *>(run.d_q) : q0p, *qb_ = q1p;
     T *bufA = static_cast<T *>(run.d_p);
@@ -644,13 +661,11 @@ void run_batch_t(Ctx &c, StepOp &op, BatchRun &run) {
         }
         if (P.n_ent > 0) {
             // the step reads q_{l-1/2} (qa) for its load; the update writes q_{l+1/2} (qb_)
-            pa.q = qa;
-            pa.qn = qb_;
-            launch_step_pml<T>(a, pa, run.B, W, nt, grid, s);
-            std::swap(qa, qb_);
-        } else {
-            launch_step<T>(a, run.B, W, nt, pk, grid, s);
+            a.pml_q = qa;
+            a.pml_qn = qb_;
         }
+        launch_step<T>(a, run.B, W, nt, pk, grid + a.pml_blocks, s);
+        if (P.n_ent > 0) std::swap(qa, qb_);
         if (flush) {
             hipLaunchKernelGGL(k_hist_flush<T>, dim3((hist_nser + 63) / 64), dim3(256), 0, s,
                                static_cast<const T *>(hist_stage), hist_nser, (int)(slot + 1),

@@ -64,13 +64,18 @@ struct StepArgs {
     double *__restrict__ acc;
     // full velocity field out: vel_out[node][col] = -(p+ - p)/dt
     T *__restrict__ vel_out;
-    // split-field PML load of node rows in the layer (pml_row >= 0):
+    // split-field PML load, row = pml_ptr[node] .. pml_ptr[node + 1]:
     //   p+[node][:] += sum_{k in row} pml_coef[k] * pml_q[pml_ent[k]][:]   (q_{l-1/2})
-    const int32_t *__restrict__ pml_row;
     const int32_t *__restrict__ pml_ptr;
     const int32_t *__restrict__ pml_ent;
     const T *__restrict__ pml_coef;
     const T *__restrict__ pml_q;
+    // the launch's first pml_blocks workgroups form q_{l+1/2} from p_l and q_{l-1/2}
+    const uint32_t *__restrict__ pml_rec;
+    T *__restrict__ pml_qn;
+    int64_t pml_n_ent;
+    int32_t pml_nv;               // nodes per element
+    int32_t pml_blocks;           // a multiple of 8
     // packed per-node records (PK launches): beta, cols, coefficients
     const uint32_t *__restrict__ meta;
     // replayed launches (a captured run of steps): the per-step quantities are this
@@ -88,24 +93,20 @@ struct StepArgs {
 // Everything after the stencil sum: the PML load and nodal loads join the increment, then
 // p_{l+1} = p_l + inc feeds the receiver taps, coarse-node histories, the adjoint
 // correlation, the velocity output and the store.
-template <typename T, int VEC, int LPN, bool NT>
+template <typename T, int VEC, int LPN, bool NT, bool PM>
 __device__ __forceinline__ void step_tail(const StepArgs<T> &a, int64_t tile, int64_t node, int ln,
                                           int sub, int64_t off,
                                           const typename VecT<T, VEC>::type &pc,
-                                          typename VecT<T, VEC>::type inc) {
+                                          typename VecT<T, VEC>::type inc, int32_t pk0, int32_t pk1) {
     typedef typename VecT<T, VEC>::type V;
     constexpr int64_t BW = VEC * LPN;                 // row stride = batch width
     const int64_t sb = a.step_base ? a.step_base[0] : 0;
-    if (a.pml_row) {
-        const int32_t pr = a.pml_row[node];
-        if (pr >= 0) {
-            const int32_t k0 = a.pml_ptr[pr], k1 = a.pml_ptr[pr + 1];
-            // unrolled so that several entry -> q gather chains are in flight
+    if constexpr (PM) {
+        // unrolled so that several entry -> q gather chains are in flight
 #pragma unroll 4
-            for (int32_t k = k0; k < k1; ++k)
-                inc += a.pml_coef[k] *
-                       *reinterpret_cast<const V *>(a.pml_q + (int64_t)a.pml_ent[k] * BW + (int64_t)sub * VEC);
-        }
+        for (int32_t k = pk0; k < pk1; ++k)
+            inc += a.pml_coef[k] *
+                   *reinterpret_cast<const V *>(a.pml_q + (int64_t)a.pml_ent[k] * BW + (int64_t)sub * VEC);
     }
 
     // nodal loads of this tile (sources, adjoint residuals, impulses)
@@ -221,11 +222,60 @@ __device__ __forceinline__ T packed_value(uint32_t lo, uint32_t hi) {
         return __hiloint2double((int)hi, (int)lo);
     }
 }
-template <typename T, int VEC, int LPN, int W, bool NT, bool PK = false, bool SP = false>
+
+// Split-field PML: q_{l+1/2} = (1 - dt zeta) q_{l-1/2} + dt d_k p_l|_T for every listed
+// element-direction; VEC columns per lane, LPN lanes per entry.  Each entry's
+// record [its NV nodes, dt d_k phi_a|_T for the NV nodes, 1 - dt zeta] (values as 1 or 2
+// 32-bit words) is contiguous, so a workgroup's records are one contiguous range: the
+// lanes copy it to LDS one word each and read their entry's words from there.
+template <typename T, int VEC, int LPN, int NV>
+__device__ __forceinline__ void pml_update(const StepArgs<T> &a, uint32_t *rec) {
+    typedef typename VecT<T, VEC>::type V;
+    constexpr int VW = sizeof(T) / 4;
+    constexpr int MW = NV + (NV + 1) * VW;
+    constexpr int64_t BW = VEC * LPN;
+    constexpr int per_block = 256 / LPN;
+    const int64_t e0 = (int64_t)blockIdx.x * per_block;
+    const int words = (int)min((int64_t)per_block, a.pml_n_ent - e0) * MW;
+    for (int w = threadIdx.x; w < words; w += 256) rec[w] = a.pml_rec[e0 * MW + w];
+    __syncthreads();
+    const int le = threadIdx.x / LPN;
+    const int64_t e = e0 + le;
+    if (e >= a.pml_n_ent) return;
+    const int64_t off = (int64_t)(threadIdx.x % LPN) * VEC;
+    const uint32_t *r = rec + le * MW;
+    auto value = [&](int k) -> T {
+        if constexpr (VW == 1) return __uint_as_float(r[k]);
+        else return __hiloint2double((int)r[k + 1], (int)r[k]);
+    };
+    V s = value(NV + NV * VW) * *reinterpret_cast<const V *>(a.pml_q + e * BW + off);
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+        s += value(NV + k * VW) * *reinterpret_cast<const V *>(a.p + (int64_t)r[k] * BW + off);
+    // streamed out: the step reads q_{l+1/2} only in the next launch, and dirty lines left
+    // in the XCDs' L2 caches would be written back at the kernel boundary
+    __builtin_nontemporal_store(s, reinterpret_cast<V *>(a.pml_qn + e * BW + off));
+}
+
+template <typename T, int VEC, int LPN, int W, bool NT, bool PK = false, bool SP = false, bool PM = false>
 __global__ __launch_bounds__(256) void k_step(const StepArgs<T> a) {
     typedef typename VecT<T, VEC>::type V;
     constexpr int S = 256 / LPN;
-    const int bid = blockIdx.x;
+    int bid = blockIdx.x;
+    // PM: the PML's update needs p_l and q_{l-1/2} alone, as the step does, and takes workgroups
+    // of the same launch.  Small meshes are bound by the latency of a launch, large ones by HBM
+    // (us a step, FP32, two launches and one): 321^2 nodes x 16 columns 12.7 and 8.8, 1,001^2 x
+    // 32 103 and 89, x 64 208 and 191.  Packed records count here as without a layer: per-slice
+    // arrays (variant 3 of the last) take 208, and a kernel apart from this one took 219.
+    if constexpr (PM) {
+        __shared__ uint32_t rec[256 / LPN * (4 + 5 * (int)(sizeof(T) / 4))];
+        if (bid < a.pml_blocks) {
+            if (a.pml_nv == 3) pml_update<T, VEC, LPN, 3>(a, rec);
+            else pml_update<T, VEC, LPN, 4>(a, rec);
+            return;
+        }
+        bid -= a.pml_blocks;
+    }
     // XCD-contiguous order (consecutive workgroup ids go to different XCDs) or linear
     const int64_t tile = a.xcd_map ? (int64_t)(bid & 7) * a.per_xcd + (bid >> 3) : (int64_t)bid;
     if (tile >= a.n_tiles) return;
@@ -233,6 +283,12 @@ __global__ __launch_bounds__(256) void k_step(const StepArgs<T> a) {
     const int sub = threadIdx.x % LPN;
     const int64_t node = tile * S + ln;
     if (node >= a.n) return;
+    // the PML row's bounds now: its gathers come last
+    int32_t pk0 = 0, pk1 = 0;
+    if constexpr (PM) {
+        pk0 = a.pml_ptr[node];
+        pk1 = a.pml_ptr[node + 1];
+    }
 
     // the row stride is the batch width VEC * LPN (a power of two: shifts, not multiplies)
     constexpr int64_t BW = VEC * LPN;
@@ -307,7 +363,7 @@ __global__ __launch_bounds__(256) void k_step(const StepArgs<T> a) {
         }
 #pragma unroll
         for (int k = 0; k < W; ++k) inc += v[k] * (pj[k] - pc);
-        step_tail<T, VEC, LPN, NT>(a, tile, node, ln, sub, off, pc, inc);
+        step_tail<T, VEC, LPN, NT, PM>(a, tile, node, ln, sub, off, pc, inc, pk0, pk1);
         return;
     }
     V pc, pv;
@@ -339,7 +395,7 @@ __global__ __launch_bounds__(256) void k_step(const StepArgs<T> a) {
             inc += vk * (pj - pc);
         }
     }
-    step_tail<T, VEC, LPN, NT>(a, tile, node, ln, sub, off, pc, inc);
+    step_tail<T, VEC, LPN, NT, PM>(a, tile, node, ln, sub, off, pc, inc, pk0, pk1);
 }
 
 // One chunk of staged histories (count <= 64 steps, stage[s][series], series = c * B + col)
@@ -373,43 +429,6 @@ __global__ void k_zero(T *__restrict__ x, int64_t count) {
 // Step base of replayed launches: base = value (set) or base += value (advance).
 __global__ void k_step_base(int64_t *__restrict__ base, int64_t value, int advance) {
     if (blockIdx.x == 0 && threadIdx.x == 0) base[0] = advance ? base[0] + value : value;
-}
-
-// Split-field PML: q_{l+1/2} = (1 - dt zeta) q_{l-1/2} + dt d_k p_l|_T for every listed
-// element-direction; VEC columns per lane, LPN = B / VEC lanes per entry.  Each entry's
-// record [its NV nodes, dt d_k phi_a|_T for the NV nodes, 1 - dt zeta] (values as 1 or 2
-// 32-bit words) is contiguous, so a workgroup's records are one contiguous range: the
-// lanes copy it to LDS one word each and read their entry's words from there.
-template <typename T, int VEC, int NV>
-__global__ __launch_bounds__(256) void k_pml_q(const uint32_t *__restrict__ ent_rec, int64_t n_ent,
-                                               int64_t B, const T *__restrict__ p,
-                                               const T *__restrict__ q, T *__restrict__ qn) {
-    typedef typename VecT<T, VEC>::type V;
-    constexpr int VW = sizeof(T) / 4;
-    constexpr int MW = NV + (NV + 1) * VW;
-    __shared__ uint32_t rec[256 * MW];
-    const int lpn = (int)(B / VEC);
-    const int per_block = 256 / lpn;
-    const int64_t e0 = (int64_t)blockIdx.x * per_block;
-    const int64_t words = std::min<int64_t>(per_block, n_ent - e0) * MW;
-    for (int64_t w = threadIdx.x; w < words; w += 256) rec[w] = ent_rec[e0 * MW + w];
-    __syncthreads();
-    const int le = threadIdx.x / lpn;
-    const int64_t e = e0 + le;
-    if (e >= n_ent) return;
-    const int64_t off = (int64_t)(threadIdx.x % lpn) * VEC;
-    const uint32_t *r = rec + le * MW;
-    auto value = [&](int k) -> T {
-        if constexpr (VW == 1) return __uint_as_float(r[k]);
-        else return __hiloint2double((int)r[k + 1], (int)r[k]);
-    };
-    V s = value(NV + NV * VW) * *reinterpret_cast<const V *>(q + e * B + off);
-#pragma unroll
-    for (int a = 0; a < NV; ++a)
-        s += value(NV + a * VW) * *reinterpret_cast<const V *>(p + (int64_t)r[a] * B + off);
-    // streamed out: the step reads q_{l+1/2} only in the next launch, and dirty lines left
-    // in the XCDs' L2 caches would be written back at the kernel boundary
-    __builtin_nontemporal_store(s, reinterpret_cast<V *>(qn + e * B + off));
 }
 
 // ------------------------------------------------------------------------------------
@@ -456,58 +475,39 @@ namespace {
 // pk: 0 = per-slice coefficient arrays, 1 = packed records, 2 = packed records with
 // speculative gathers.  The packed launches exist for FP32 and FP64 records of at most
 // eight words per lane; elsewhere the plain one runs (identical results).
-template <typename T, int VEC, int LPN, int W, bool NT>
+template <typename T, int VEC, int LPN, int W, bool NT, bool PM>
 void launch_step_pk(const StepArgs<T> &a, int pk, int64_t grid, hipStream_t s) {
-    if constexpr (PackedRecord<T, W>::words <= 8 * LPN) {
-        if (pk == 2) {
-            hipLaunchKernelGGL((k_step<T, VEC, LPN, W, NT, true, true>), dim3(grid), dim3(256), 0, s, a);
-            return;
-        }
-        if (pk == 1) {
-            hipLaunchKernelGGL((k_step<T, VEC, LPN, W, NT, true>), dim3(grid), dim3(256), 0, s, a);
-            return;
-        }
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, a); };
+    if constexpr ((W == 4 || W == 6) && PackedRecord<T, W>::words <= 8 * LPN) {
+        if (pk == 2) return go(k_step<T, VEC, LPN, W, NT, true, true, PM>);
+        if (pk == 1) return go(k_step<T, VEC, LPN, W, NT, true, false, PM>);
     }
     (void)pk;
-    hipLaunchKernelGGL((k_step<T, VEC, LPN, W, NT, false>), dim3(grid), dim3(256), 0, s, a);
+    go(k_step<T, VEC, LPN, W, NT, false, false, PM>);
 }
 
-template <typename T, int VEC, int LPN, bool NT>
+template <typename T, int VEC, int LPN, bool NT, bool PM>
 void launch_step_w(const StepArgs<T> &a, int W, int pk, int64_t grid, hipStream_t s) {
     switch (W) {
-    case 4: launch_step_pk<T, VEC, LPN, 4, NT>(a, pk, grid, s); break;
-    case 6: launch_step_pk<T, VEC, LPN, 6, NT>(a, pk, grid, s); break;
-    case 8: hipLaunchKernelGGL((k_step<T, VEC, LPN, 8, NT>), dim3(grid), dim3(256), 0, s, a); break;
-    case 12: hipLaunchKernelGGL((k_step<T, VEC, LPN, 12, NT>), dim3(grid), dim3(256), 0, s, a); break;
-    case 16: hipLaunchKernelGGL((k_step<T, VEC, LPN, 16, NT>), dim3(grid), dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL((k_step<T, VEC, LPN, 0, NT>), dim3(grid), dim3(256), 0, s, a); break;
+    case 4: launch_step_pk<T, VEC, LPN, 4, NT, PM>(a, pk, grid, s); break;
+    case 6: launch_step_pk<T, VEC, LPN, 6, NT, PM>(a, pk, grid, s); break;
+    case 8: launch_step_pk<T, VEC, LPN, 8, NT, PM>(a, pk, grid, s); break;
+    case 12: launch_step_pk<T, VEC, LPN, 12, NT, PM>(a, pk, grid, s); break;
+    case 16: launch_step_pk<T, VEC, LPN, 16, NT, PM>(a, pk, grid, s); break;
+    default: launch_step_pk<T, VEC, LPN, 0, NT, PM>(a, pk, grid, s); break;
     }
 }
 
 template <typename T, int VEC, int LPN>
 void launch_step_t(const StepArgs<T> &a, int W, bool nt, int pk, int64_t grid, hipStream_t s) {
     MGRT_REQUIRE(a.B == VEC * LPN, MGRT_E_ARG, "row stride must equal the batch width");
-    if (nt) launch_step_w<T, VEC, LPN, true>(a, W, pk, grid, s);
-    else launch_step_w<T, VEC, LPN, false>(a, W, pk, grid, s);
-}
-
-template <typename T, int VEC>
-void launch_pml_q_v(int d, const PmlOp &P, int B, int64_t g, const T *p, const T *q, T *qn,
-                    hipStream_t s) {
-    if (d == 2)
-        hipLaunchKernelGGL((k_pml_q<T, VEC, 3>), dim3(g), dim3(256), 0, s, P.ent_rec.as<uint32_t>(),
-                           P.n_ent, (int64_t)B, p, q, qn);
-    else
-        hipLaunchKernelGGL((k_pml_q<T, VEC, 4>), dim3(g), dim3(256), 0, s, P.ent_rec.as<uint32_t>(),
-                           P.n_ent, (int64_t)B, p, q, qn);
-}
-
-template <typename T>
-void launch_pml_q(int d, int vec, const PmlOp &P, int B, int64_t g, const T *p, const T *q, T *qn,
-                  hipStream_t s) {
-    if (vec == 4) launch_pml_q_v<T, 4>(d, P, B, g, p, q, qn, s);
-    else if (vec == 2) launch_pml_q_v<T, 2>(d, P, B, g, p, q, qn, s);
-    else launch_pml_q_v<T, 1>(d, P, B, g, p, q, qn, s);
+    if (a.pml_blocks) {
+        if (nt) launch_step_w<T, VEC, LPN, true, true>(a, W, pk, grid, s);
+        else launch_step_w<T, VEC, LPN, false, true>(a, W, pk, grid, s);
+    } else {
+        if (nt) launch_step_w<T, VEC, LPN, true, false>(a, W, pk, grid, s);
+        else launch_step_w<T, VEC, LPN, false, false>(a, W, pk, grid, s);
+    }
 }
 
 template <typename T>
