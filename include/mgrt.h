@@ -202,7 +202,8 @@ int mgrt_stability_bound(mgrt_ctx *ctx, double *dt_max);
  * wave a strip of a lexicographic 2D grid (the same node updates; a run of several columns
  * gives the one-step launches' values bit for bit, a one-column run on up to 65,536 nodes
  * agrees with them to rounding).  One launch per step stays for runs of several columns below
- * 256 steps, a requested launch variant or batch width above 1, 3D meshes beyond some 100,000
+ * 256 steps, one-column runs on more nodes until their steps on the mesh repay the tables (64
+ * steps, and a hundredth of the nodes beyond 140,000), a requested launch variant or batch width above 1, 3D meshes beyond some 100,000
  * words of state, tiles with more than 64 loads or taps of a column group, and
  * MGRT_F_ONE_STEP (mgrt_timing.steps_per_launch reports which ran). */
 int mgrt_forward_traces(mgrt_ctx *ctx, int64_t n_src, const double *src_xyz, int32_t n_rec,

@@ -206,7 +206,7 @@ static std::vector<double> forward_impl(Ctx &c, const Acquisition &aq, const dou
         const int B = pick_batch(c, prec, aq.n_src, opts ? opts->batch : 0, dt, flags);
         const int S = tile_nodes(prec, B);
         StepOp &op = get_step_op(c, S, prec, dt);
-        const Blocks *blocks = plan_blocks(c, prec, op, std::min<int64_t>(B, aq.n_src), B, n_steps, opts);
+        Blocks *blocks = plan_blocks(c, prec, op, std::min<int64_t>(B, aq.n_src), B, n_steps, opts);
         const size_t esz = prec == 32 ? 4 : 8;
         DevBuf series = upload(g, c.stream);
         DevBuf bufA(n * B * esz), bufB(n * B * esz);
@@ -478,6 +478,7 @@ int mgrt_upload_mesh(mgrt_ctx *ctx, int dim, int64_t n_nodes, const double *coor
         c.tuned.clear();
         c.batch_tuned.clear();
         c.blocks.clear();
+        c.one_col_steps = 0;
         c.grid_nx = -1;
         build_host_mesh(c.hm, dim, n_nodes, coords, n_elems, elems, n_bfacets, bfacets, admittance,
                         n_coarse, coarse_of_elem, coarse_verts);

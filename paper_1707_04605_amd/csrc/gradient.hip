@@ -104,12 +104,12 @@ void gradient_t(Ctx &c, const Acquisition &aq, const std::vector<double> &g, dou
     // GB written).  One FP32 column on a small mesh keeps its segments: its
     // checkpointed sweep rounds as one-column runs do, the recomputation as the adjoint does.
     const size_t room = std::min(opts && opts->mem_budget_gb > 0 ? cap : cap / 2, CACHE_BYTES / 4 * 3);
-    const bool one_col32 = prec == 32 && B == 1 && n <= 65536;
+    const bool one_col32 = prec == 32 && B == 1 && n <= ONE_COLUMN_NODES;
     if (!one_col32 && bytes(N, B) + (size_t)n * 8 <= room) K = N;
     // several steps per launch for the forward and the adjoint sweep alike (they share the
     // velocity's layout), where their second buffer pairs fit too
     const int64_t cols = std::min<int64_t>(B, aq.n_src);
-    const Blocks *fwd_blocks = nullptr, *adj_blocks = nullptr;
+    Blocks *fwd_blocks = nullptr, *adj_blocks = nullptr;
     if (bytes(K, B) + (size_t)n * 8 + (4 + cols) * slab <= cap) {
         fwd_blocks = plan_blocks(c, prec, op, cols, B, N, opts);
         adj_blocks = fwd_blocks ? plan_blocks(c, prec, op, cols, B, N, opts, true) : nullptr;

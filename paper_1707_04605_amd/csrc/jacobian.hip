@@ -352,7 +352,7 @@ void jacobian_mg(Ctx &c, const Acquisition &aq, const std::vector<double> &g,
     StepOp &opf = get_step_op(c, tile_nodes(prec, Bf), prec, dt);
     // several steps per launch where their second pair of state buffers also fits the plan
     const bool room = need(Bf, Bi) + (nsets == 2 ? set_bytes : 0) + (size_t)n * esz * 2 * std::max(Bf, Bi) <= cap;
-    const Blocks *blocks = room ? plan_blocks(c, prec, opf, std::min<int64_t>(Bf, aq.n_src), Bf, N, opts) : nullptr;
+    Blocks *blocks = room ? plan_blocks(c, prec, opf, std::min<int64_t>(Bf, aq.n_src), Bf, N, opts) : nullptr;
     MGRT_HIP(hipFuncSetAttribute((const void *)k_corr<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     if (mono) {
         // One run per source batch with w1 at the source points: the field to lh, the
@@ -420,7 +420,7 @@ void jacobian_mg(Ctx &c, const Acquisition &aq, const std::vector<double> &g,
         // impulse runs from the receivers of this source batch
         const int64_t P = (int64_t)nb * aq.n_rec;
         StepOp &opi = get_step_op(c, tile_nodes(prec, Bi), prec, dt);
-        const Blocks *iblocks = room ? plan_blocks(c, prec, opi, std::min<int64_t>(Bi, P), Bi, N, opts) : nullptr;
+        Blocks *iblocks = room ? plan_blocks(c, prec, opi, std::min<int64_t>(Bi, P), Bi, N, opts) : nullptr;
         for (int64_t q0 = 0; q0 < P; q0 += Bi) {
             const int nq = (int)std::min<int64_t>(Bi, P - q0);
             BatchRun ir;

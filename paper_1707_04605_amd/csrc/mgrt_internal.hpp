@@ -144,12 +144,16 @@ inline T *put(Arena &ar, const std::vector<T> &v) {
 }
 
 template <typename T>
-inline DevBuf upload(const std::vector<T> &v, hipStream_t s) {
-    // blocking copy: the host vector may be freed as soon as this returns
+inline DevBuf upload(const T *v, size_t count, hipStream_t s) {
+    // blocking copy: the host array may be freed as soon as this returns
     (void)s;
-    DevBuf b(v.size() * sizeof(T));
-    if (!v.empty()) MGRT_HIP(hipMemcpy(b.p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
+    DevBuf b(count * sizeof(T));
+    if (count) MGRT_HIP(hipMemcpy(b.p, v, count * sizeof(T), hipMemcpyHostToDevice));
     return b;
+}
+template <typename T>
+inline DevBuf upload(const std::vector<T> &v, hipStream_t s) {
+    return upload(v.data(), v.size(), s);
 }
 
 // Several host arrays copied to the device in one piece (a blocking copy costs 13 us whatever
@@ -289,6 +293,11 @@ struct Tuned {
     double best_us = 0;
 };
 
+// One-column runs on meshes up to this size have always taken several steps per launch and summed
+// a node's terms in an order of their own there (multistep.hip, beta_first).  Their values stay
+// what they were; larger meshes and runs of several columns have the one-step launches' order.
+constexpr int64_t ONE_COLUMN_NODES = 65536;
+
 struct Blocks;             // multistep.hip: tiles and regions of several-steps launches
 
 struct Ctx {
@@ -314,6 +323,7 @@ struct Ctx {
     // (strips, precision, columns a group, padded row width, tiles asked for or (strips) groups,
     // steps a launch) -> regions or strips; dropped with the mesh
     std::map<std::tuple<bool, int, int, int, int64_t, int>, std::shared_ptr<Blocks>> blocks;
+    int64_t one_col_steps = 0;         // steps of one-column runs so far that had no tables (plan_blocks)
     int64_t grid_nx = -1;              // row length of a lexicographic 2D grid, 0: none, -1: not looked at
     std::shared_ptr<void> fft_plans;   // deconv.hip: FFT plans kept per (length, batch, precision)
     mgrt_timing timing{};
@@ -387,7 +397,7 @@ struct BatchRun {
     // are launched directly (no graph, no tuning, no per-launch events)
     Arena *arena = nullptr;
     // several steps per launch on these regions (plan_blocks); null: one launch per step
-    const Blocks *blocks = nullptr;
+    Blocks *blocks = nullptr;
     void *d_alt_p = nullptr, *d_alt_pm = nullptr;   // their second buffer pair (null: allocated
                                                     // by the run, which without room for it
                                                     // takes one launch per step)
@@ -399,7 +409,7 @@ int64_t pml_entries(const Ctx &c);
 Blocks *plan_blocks(Ctx &c, int prec, const StepOp &op, int64_t n_cols, int B, int64_t n_steps,
                     const mgrt_run_opts *opts, bool corr = false);
 // whether the loads and taps of run fit the regions' lists
-bool blocks_hold(const Ctx &c, const Blocks &B, const BatchRun &run);
+bool blocks_hold(const Ctx &c, Blocks &B, const BatchRun &run);
 // false: the lists do not fit (nothing ran)
 bool run_blocks(Ctx &c, StepOp &op, BatchRun &run);
 // step.hip: move a chunk of count staged history steps, the last of the *done steps so

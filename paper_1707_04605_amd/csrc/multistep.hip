@@ -22,7 +22,12 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <cstdlib>
+#include <iterator>
+#include <map>
 #include <memory>
+#include <new>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -39,19 +44,61 @@ struct Blocks {
     DevBuf cnt;      // int32 [n_tiles][64]: entries of the tile within distance d
     DevBuf node;     // int32 per entry: stepping-order node (padding: the tile's first)
     DevBuf nbr;      // uint32 [W/2][n_ent]: LDS byte offsets of the row's neighbours, in pairs
-    // where a node is updated: (tile, local entry) of every region that holds it within
-    // distance k - 1, the node's own tile marked by own[]
-    std::vector<int64_t> at_ptr;
-    std::vector<int32_t> at_tile, at_loc;
-    std::vector<uint8_t> own;
+    // on the host: each node's tile, the tiles' entries and how many lie within each distance
+    std::vector<int32_t> tile_of, h_cnt;             // h_cnt [n_tiles][k + 1]
+    std::vector<std::vector<int32_t>> ents;
     // strips instead of regions (strips.hpp): nx > 0, tiles are strips x chunks of rows
     int64_t nx = 0, ny = 0, strips = 0, chunks = 0;
 
+    // where a region updates a node: its tile, the local entry, whether the tile is the node's own
+    struct Place {
+        int32_t tile, loc;
+        bool own;
+    };
+    // places of the nodes that carried loads or taps so far
+    std::map<int32_t, std::vector<Place>> places;
+
+    // A tile updates the nodes within distance k - 1 of it, so the tiles that update node ii are
+    // those of the nodes within distance k - 1 of ii.
+    const std::vector<Place> &places_of(const HostMesh &hm, int32_t ii) {
+        const auto it = places.find(ii);
+        if (it != places.end()) return it->second;
+        std::vector<int32_t> ball{ii}, seen{ii}, tiles;
+        std::vector<Place> out;
+        size_t f0 = 0;
+        for (int d = 0; d < k; ++d) {
+            const size_t f1 = ball.size();
+            for (size_t f = f0; f < f1; ++f) {
+                const int32_t t = tile_of[ball[f]];
+                if (std::find(tiles.begin(), tiles.end(), t) != tiles.end()) continue;
+                tiles.push_back(t);
+                // the entries at distance d of the tile, ascending
+                const int32_t *ct = &h_cnt[(size_t)t * (k + 1)];
+                const auto e0 = ents[t].begin() + (d ? ct[d - 1] : 0), e1 = ents[t].begin() + ct[d];
+                out.push_back(Place{t, (int32_t)(std::lower_bound(e0, e1, ii) - ents[t].begin()), d == 0});
+            }
+            if (n_tiles == 1) break;
+            std::vector<int32_t> next;
+            for (size_t f = f0; f < f1; ++f) {
+                const int64_t i = hm.perm[ball[f]];
+                for (int64_t q = hm.krow[i]; q < hm.krow[i + 1]; ++q) next.push_back(hm.iperm[hm.kcol[q]]);
+            }
+            std::sort(next.begin(), next.end());
+            next.erase(std::unique(next.begin(), next.end()), next.end());
+            std::vector<int32_t> all;
+            std::set_difference(next.begin(), next.end(), seen.begin(), seen.end(), std::back_inserter(ball));
+            std::set_union(seen.begin(), seen.end(), next.begin(), next.end(), std::back_inserter(all));
+            seen.swap(all);
+            f0 = f1;
+        }
+        return places.emplace(ii, std::move(out)).first->second;
+    }
+
     // f(tile, local entry, own) for every tile that updates node ii
     template <typename F>
-    void each_tile(int32_t ii, F &&f) const {
+    void each_tile(const HostMesh &hm, int32_t ii, F &&f) {
         if (nx == 0) {
-            for (int64_t q = at_ptr[ii]; q < at_ptr[ii + 1]; ++q) f((int64_t)at_tile[q], at_loc[q], own[q] != 0);
+            for (const Place &q : places_of(hm, ii)) f((int64_t)q.tile, q.loc, q.own);
             return;
         }
         const int64_t x = ii % nx, y = ii / nx;
@@ -450,89 +497,140 @@ void launch_blocks(const BlockArgs<T> &a, BlockLaunch &L) {
     }
 }
 
-// Cut idx[lo, hi) into nt tiles of nearly equal size by bisection along the longest side;
-// ties on that coordinate are ordered by the others and the node id, so that a cut through
-// a grid line leaves one step in it.
-void bisect(const HostMesh &hm, std::vector<int32_t> &idx, int64_t lo, int64_t hi, int64_t nt, int64_t t0,
-            std::vector<int32_t> &tile_of, int depth) {
-    if (nt == 1) {
-        for (int64_t i = lo; i < hi; ++i) tile_of[idx[i]] = (int32_t)t0;
-        return;
-    }
-    const int d = hm.d;
-    auto x = [&](int32_t ii, int a) { return hm.coords[(int64_t)hm.perm[ii] * d + a]; };
-    double mn[3], mx[3];
-    for (int a = 0; a < d; ++a) mn[a] = mx[a] = x(idx[lo], a);
-    for (int64_t i = lo; i < hi; ++i)
-        for (int a = 0; a < d; ++a) {
-            const double c = x(idx[i], a);
-            mn[a] = std::min(mn[a], c);
-            mx[a] = std::max(mx[a], c);
-        }
-    int ax = d - 1;
-    for (int a = d - 2; a >= 0; --a)
-        if (mx[a] - mn[a] > 1.0001 * (mx[ax] - mn[ax])) ax = a;
-    const int64_t nl = nt / 2, mid = lo + (hi - lo) * nl / nt;
-    std::nth_element(idx.begin() + lo, idx.begin() + mid, idx.begin() + hi, [&](int32_t p, int32_t q) {
-        for (int b = 0; b < d; ++b) {
-            const int a = (ax + b) % d;
-            const double xp = x(p, a), xq = x(q, a);
-            if (xp != xq) return xp < xq;
-        }
-        return p < q;
-    });
-    if (depth < 4 && hi - lo > 16384) {
-        std::thread th([&] { bisect(hm, idx, lo, mid, nl, t0, tile_of, depth + 1); });
-        bisect(hm, idx, mid, hi, nt - nl, t0 + nl, tile_of, depth + 1);
-        th.join();
-    } else {
-        bisect(hm, idx, lo, mid, nl, t0, tile_of, depth + 1);
-        bisect(hm, idx, mid, hi, nt - nl, t0 + nl, tile_of, depth + 1);
-    }
+// Entries of a region of s nodes with k rings of the nearest-neighbour stencil of a square
+// or cubic tile (a start for the tile size; the built regions decide).
+double region_estimate(int d, double s, int k) {
+    if (d == 2) return s + 4.0 * k * std::sqrt(s) * 1.03 + 2.0 * k * (k - 1);
+    const double a = std::cbrt(s) * 1.02;
+    double r = s;
+    for (int q = 1; q <= k; ++q) r += 6 * a * a + 12.0 * a * (q - 1) + 4.0 * (q - 1) * (q - 2);
+    return r;
 }
 
+// A node on the host: its coordinates beside its id, so that a cut reads its keys in a row.
+template <int D>
+struct NodeAt {
+    double x[D];
+    int32_t ii;
+};
+
+// Cut nodes[lo, hi) into nt tiles of nearly equal size by bisection along the longest side;
+// ties on that coordinate are ordered by the others and the node id, so that a cut through
+// a grid line leaves one step in it.  first[t0 + t] is where tile t of them starts.
+template <int D>
+void bisect(NodeAt<D> *nodes, int64_t lo, int64_t hi, int64_t nt, int64_t t0, int64_t *first, int depth) {
+    if (nt == 1) {
+        first[t0] = lo;
+        return;
+    }
+    double mn[D], mx[D];
+    for (int a = 0; a < D; ++a) mn[a] = mx[a] = nodes[lo].x[a];
+    for (int64_t i = lo; i < hi; ++i)
+        for (int a = 0; a < D; ++a) {
+            mn[a] = std::min(mn[a], nodes[i].x[a]);
+            mx[a] = std::max(mx[a], nodes[i].x[a]);
+        }
+    int ax = D - 1;
+    for (int a = D - 2; a >= 0; --a)
+        if (mx[a] - mn[a] > 1.0001 * (mx[ax] - mn[ax])) ax = a;
+    const int64_t nl = nt / 2, mid = lo + (hi - lo) * nl / nt;
+    std::nth_element(nodes + lo, nodes + mid, nodes + hi, [ax](const NodeAt<D> &p, const NodeAt<D> &q) {
+        for (int b = 0; b < D; ++b) {
+            const int a = ax + b < D ? ax + b : ax + b - D;
+            if (p.x[a] != q.x[a]) return p.x[a] < q.x[a];
+        }
+        return p.ii < q.ii;
+    });
+    std::thread half;
+    if (depth < 4 && hi - lo > 2048) {
+        try {
+            half = std::thread([=] { bisect<D>(nodes, lo, mid, nl, t0, first, depth + 1); });
+        } catch (const std::system_error &) {       // no thread to be had: this one does both
+        }
+    }
+    if (!half.joinable()) bisect<D>(nodes, lo, mid, nl, t0, first, depth + 1);
+    bisect<D>(nodes, mid, hi, nt - nl, t0 + nl, first, depth + 1);
+    if (half.joinable()) half.join();
+}
+
+// The tiles' nodes, tile by tile, and where each tile starts.
+template <int D>
+void cut_tiles(const HostMesh &hm, int64_t n_tiles, std::vector<int32_t> &idx, std::vector<int64_t> &first) {
+    const int64_t n = hm.n;
+    const std::unique_ptr<NodeAt<D>[]> nodes(new NodeAt<D>[n]);
+    parallel_for(n, [&](int64_t i0, int64_t i1) {
+        for (int64_t i = i0; i < i1; ++i) {
+            for (int a = 0; a < D; ++a) nodes[i].x[a] = hm.coords[(int64_t)hm.perm[i] * D + a];
+            nodes[i].ii = (int32_t)i;
+        }
+    }, 16384);
+    first.assign(n_tiles + 1, n);
+    bisect<D>(nodes.get(), 0, n, n_tiles, 0, first.data(), 0);
+    idx.resize(n);
+    parallel_for(n, [&](int64_t i0, int64_t i1) {
+        for (int64_t i = i0; i < i1; ++i) idx[i] = nodes[i].ii;
+    }, 65536);
+}
+
+// The last region that met a node (its tile + 1, 0: none) and the node's entry there; zero pages
+// of the allocation that no region of the thread touches are never made.
+struct Mark {
+    int32_t tile, loc;
+};
+struct FreeHost {
+    void operator()(void *p) const { std::free(p); }
+};
+
 // Regions of n_tiles tiles and k steps: per tile the entries by distance, ascending within
-// a distance.  Returns null when a region has more than cap entries.
+// a distance.  Returns null when a region has more than cap entries.  The first run of a mesh
+// and shape waits for this (eight cores, a node table per thread, every node's tiles listed and
+// tile numbers tried that did not fit: 301^2 nodes 13 ms, 1,025^2 204; as here 4.6 and 37).
 std::shared_ptr<Blocks> build_blocks(Ctx &c, int W, int64_t n_tiles, int k, int cap, int npt_max, int entry_bytes,
                                      int c_esz) {
     const HostMesh &hm = c.hm;
     const int64_t n = hm.n;
-    std::vector<int32_t> idx(n), tile_of(n);
-    for (int64_t i = 0; i < n; ++i) idx[i] = (int32_t)i;
-    bisect(hm, idx, 0, n, n_tiles, 0, tile_of, 0);
-    // the tiles' nodes, ascending
-    std::vector<int64_t> tptr(n_tiles + 1, 0);
-    for (int64_t i = 0; i < n; ++i) tptr[tile_of[i] + 1]++;
-    for (int64_t t = 0; t < n_tiles; ++t) tptr[t + 1] += tptr[t];
-    {
-        std::vector<int64_t> fill(tptr.begin(), tptr.end() - 1);
-        for (int64_t i = 0; i < n; ++i) idx[fill[tile_of[i]]++] = (int32_t)i;
-    }
-    std::vector<std::vector<int32_t>> ents(n_tiles);
-    std::vector<int32_t> cnt((size_t)n_tiles * (k + 1), 0);
-    std::vector<std::vector<uint32_t>> nbs(n_tiles);
+    std::vector<int32_t> idx;
+    std::vector<int64_t> first;
+    if (hm.d == 2) cut_tiles<2>(hm, n_tiles, idx, first);
+    else cut_tiles<3>(hm, n_tiles, idx, first);
+    auto B = std::make_shared<Blocks>();
+    B->k = k;
+    B->W = W;
+    B->n_tiles = n_tiles;
+    B->tile_of.resize(n);
+    B->h_cnt.assign((size_t)n_tiles * (k + 1), 0);
+    B->ents.resize(n_tiles);
+    std::vector<std::vector<uint16_t>> nbs(n_tiles);       // [entry][W]: LDS byte offsets
     std::atomic<int> bad{0};
-    const int W2 = W / 2;
+    // a thread costs as much as some 2,000 entries
+    const int64_t grain = std::max<int64_t>(
+        {1, n_tiles / 16, (int64_t)(2048 / std::min<double>(n, region_estimate(hm.d, (double)n / n_tiles, k)))});
     parallel_for(n_tiles, [&](int64_t a0, int64_t a1) {
         try {
-            std::vector<int32_t> stamp(n, -1), loc(n);
+            const std::unique_ptr<Mark[], FreeHost> marks(static_cast<Mark *>(std::calloc(n, sizeof(Mark))));
+            if (!marks) throw std::bad_alloc();
+            Mark *at = marks.get();
             for (int64_t t = a0; t < a1 && !bad; ++t) {
-                auto &E = ents[t];
-                int32_t *ct = &cnt[(size_t)t * (k + 1)];
-                for (int64_t q = tptr[t]; q < tptr[t + 1]; ++q) {
-                    stamp[idx[q]] = (int32_t)t;
-                    E.push_back(idx[q]);
+                const int32_t me = (int32_t)t + 1;
+                auto &E = B->ents[t];
+                int32_t *ct = &B->h_cnt[(size_t)t * (k + 1)];
+                E.reserve(std::min<int64_t>(cap + 64, 4 * (first[t + 1] - first[t]) + 256));
+                E.assign(idx.begin() + first[t], idx.begin() + first[t + 1]);
+                std::sort(E.begin(), E.end());
+                for (int32_t ii : E) {
+                    at[ii].tile = me;
+                    B->tile_of[ii] = (int32_t)t;
                 }
                 ct[0] = (int32_t)E.size();
                 size_t f0 = 0;
-                for (int d = 1; d <= k; ++d) {
+                for (int d = 1; d <= k && (int64_t)E.size() <= cap; ++d) {
                     const size_t f1 = E.size();
                     for (size_t f = f0; f < f1; ++f) {
                         const int64_t i = hm.perm[E[f]];
                         for (int64_t q = hm.krow[i]; q < hm.krow[i + 1]; ++q) {
                             const int32_t jj = hm.iperm[hm.kcol[q]];
-                            if (stamp[jj] == (int32_t)t) continue;
-                            stamp[jj] = (int32_t)t;
+                            if (at[jj].tile == me) continue;
+                            at[jj].tile = me;
                             E.push_back(jj);
                         }
                     }
@@ -544,34 +642,27 @@ std::shared_ptr<Blocks> build_blocks(Ctx &c, int W, int64_t n_tiles, int k, int 
                     bad = 1;
                     return;
                 }
-                for (size_t e = 0; e < E.size(); ++e) loc[E[e]] = (int32_t)e;
+                for (size_t e = 0; e < E.size(); ++e) at[E[e]].loc = (int32_t)e;
                 auto &N = nbs[t];
-                N.assign(E.size() * W2, 0);
+                N.resize(E.size() * W);
                 for (size_t e = 0; e < E.size(); ++e) {
-                    const int64_t i = hm.perm[E[e]];
-                    const int64_t len = hm.krow[i + 1] - hm.krow[i];
-                    for (int w = 0; w < W; ++w) {
-                        // entries at distance k are never updated; padding: the own slot
-                        uint32_t s = (uint32_t)e;
-                        if (w < len && (int)e < ct[k - 1]) s = (uint32_t)loc[hm.iperm[hm.kcol[hm.krow[i] + w]]];
-                        N[e * W2 + w / 2] |= s * entry_bytes << (w & 1 ? 16 : 0);
-                    }
+                    // entries at distance k are never updated; padding: the own slot
+                    const int64_t i = hm.perm[E[e]], q0 = hm.krow[i];
+                    const int len = (int)e < ct[k - 1] ? (int)(hm.krow[i + 1] - q0) : 0;
+                    for (int w = 0; w < W; ++w)
+                        N[e * W + w] = (uint16_t)((w < len ? at[hm.iperm[hm.kcol[q0 + w]]].loc : (int)e) * entry_bytes);
                 }
             }
         } catch (...) {
             bad = 2;
         }
-    }, std::max<int64_t>(1, n_tiles / 16));
+    }, grain);
     if (bad == 2) throw Error(MGRT_E_OOM_PLAN, "host allocation failed");
     if (bad) return nullptr;
-    auto B = std::make_shared<Blocks>();
-    B->k = k;
-    B->W = W;
-    B->n_tiles = n_tiles;
     int64_t tot = 0;
     for (int64_t t = 0; t < n_tiles; ++t) {
-        B->rmax = std::max(B->rmax, (int)ents[t].size());
-        tot += (int64_t)ents[t].size();
+        B->rmax = std::max(B->rmax, (int)B->ents[t].size());
+        tot += (int64_t)B->ents[t].size();
     }
     B->ratio = (double)tot / n;
     // 1,024 lanes a workgroup, but 512 (two workgroups a CU) for the large regions of four FP32
@@ -582,38 +673,26 @@ std::shared_ptr<Blocks> build_blocks(Ctx &c, int W, int64_t n_tiles, int k, int 
     B->threads = ((B->rmax + B->npt - 1) / B->npt + 63) / 64 * 64;
     const int64_t rp = (int64_t)B->threads * B->npt, ne = B->n_ent = n_tiles * rp;
     if (ne >= (int64_t)1 << 31) return nullptr;
-    std::vector<int32_t> node(ne), cnt64((size_t)n_tiles * 64, 0);
-    std::vector<uint32_t> nbr((size_t)ne * W2, 0);
+    const int W2 = W / 2;
+    const std::unique_ptr<int32_t[]> node(new int32_t[ne]), cnt64(new int32_t[n_tiles * 64]);
+    const std::unique_ptr<uint32_t[]> nbr(new uint32_t[(size_t)ne * W2]);
     parallel_for(n_tiles, [&](int64_t a0, int64_t a1) {
         for (int64_t t = a0; t < a1; ++t) {
-            for (int d = 0; d < 64; ++d) cnt64[t * 64 + d] = cnt[(size_t)t * (k + 1) + std::min(d, k)];
-            for (int64_t e = 0; e < rp; ++e) {
-                const bool in = e < (int64_t)ents[t].size();
-                node[t * rp + e] = ents[t][in ? e : 0];
-                for (int w = 0; in && w < W2; ++w) nbr[(size_t)w * ne + t * rp + e] = nbs[t][e * W2 + w];
+            const auto &E = B->ents[t];
+            const int64_t ec = (int64_t)E.size();
+            for (int d = 0; d < 64; ++d) cnt64[t * 64 + d] = B->h_cnt[(size_t)t * (k + 1) + std::min(d, k)];
+            for (int64_t e = 0; e < rp; ++e) node[t * rp + e] = E[e < ec ? e : 0];
+            for (int w = 0; w < W2; ++w) {
+                uint32_t *dst = nbr.get() + (size_t)w * ne + t * rp;
+                const uint16_t *src = nbs[t].data() + 2 * w;
+                for (int64_t e = 0; e < ec; ++e) dst[e] = src[e * W] | (uint32_t)src[e * W + 1] << 16;
+                std::fill(dst + ec, dst + rp, 0u);
             }
         }
-    }, 16);
-    B->at_ptr.assign(n + 1, 0);
-    for (int64_t t = 0; t < n_tiles; ++t)
-        for (int e = 0; e < cnt[(size_t)t * (k + 1) + k - 1]; ++e) B->at_ptr[ents[t][e] + 1]++;
-    for (int64_t i = 0; i < n; ++i) B->at_ptr[i + 1] += B->at_ptr[i];
-    B->at_tile.resize(B->at_ptr[n]);
-    B->at_loc.resize(B->at_ptr[n]);
-    B->own.resize(B->at_ptr[n]);
-    {
-        std::vector<int64_t> fill(B->at_ptr.begin(), B->at_ptr.end() - 1);
-        for (int64_t t = 0; t < n_tiles; ++t)
-            for (int e = 0; e < cnt[(size_t)t * (k + 1) + k - 1]; ++e) {
-                const int64_t q = fill[ents[t][e]]++;
-                B->at_tile[q] = (int32_t)t;
-                B->at_loc[q] = e;
-                B->own[q] = e < cnt[(size_t)t * (k + 1)];
-            }
-    }
-    B->cnt = upload(cnt64, c.stream);
-    B->node = upload(node, c.stream);
-    B->nbr = upload(nbr, c.stream);
+    }, std::max<int64_t>(grain, 65536 / rp));
+    B->cnt = upload(cnt64.get(), n_tiles * 64, c.stream);
+    B->node = upload(node.get(), ne, c.stream);
+    B->nbr = upload(nbr.get(), ne * W2, c.stream);
     return B;
 }
 
@@ -642,21 +721,6 @@ int64_t grid_row(const HostMesh &hm) {
     return bad ? 0 : nx;
 }
 
-// Entries of a region of s nodes with k rings of the nearest-neighbour stencil of a square
-// or cubic tile (a start for the tile size; the built regions decide).
-double region_estimate(int d, double s, int k) {
-    if (d == 2) return s + 4.0 * k * std::sqrt(s) * 1.03 + 2.0 * k * (k - 1);
-    const double a = std::cbrt(s) * 1.02;
-    double r = s;
-    for (int q = 1; q <= k; ++q) r += 6 * a * a + 12.0 * a * (q - 1) + 4.0 * (q - 1) * (q - 2);
-    return r;
-}
-
-
-}  // namespace
-
-namespace {
-
 // Cost of a launch of strips in row iterations of a SIMD: chunks of rows per strip are waves,
 // `slots` of them resident on the chip; a SIMD steps r resident waves in r iterations' time
 // (one alone takes 1.35: its LDS waits are exposed).  The rows a chunk shares with its
@@ -681,6 +745,10 @@ double strip_cost(int64_t waves, int64_t slots, double rows, int k) {
 //  - k = 12 where a tile holds up to 200 nodes (65^2 x 4: 0.80, k = 8 0.90) and for one
 //    column (129^2: 0.64, k = 8 0.89), else 8.  One-column runs on fewer than 2,048 nodes stay
 //    at 8, the bound that mgrt_timing.steps_per_launch has had there.
+//  - one column on more than 65,536 nodes, whose values are the same either way: not before the
+//    mesh's runs together repay the tables (first call, one step a launch and these, ms: 301^2
+//    nodes, 200 steps 7.3 and 4.7; 513^2, 200 7.5 and 8.8, 4,000 19.3 and 14.0; 701^2, 1,000 15.6
+//    and 19.8, 4,000 25.4 and 24.4; 1,025^2, 4,000 50 and 59; 8 steps on 301^2 1.8 and 4.6)
 //  - 3D and wide rows: a tile's rings outgrow it, so only small problems, up to 100,000 words
 //    of state per field (18^3 nodes: 1 column 3.9 -> 1.7, 16 FP32 columns 3.8 -> 2.7; 34^3 x 16
 //    loses, 4.3 -> 7.6), with k = 4, above 60,000 words 3
@@ -704,7 +772,13 @@ Blocks *plan_blocks(Ctx &c, int prec, const StepOp &op, int64_t n_cols, int B, i
     auto lookup = [&](bool strip, int64_t a, auto &&build) -> Blocks * {
         const auto key = std::make_tuple(strip, prec, vec, W, a, k);
         auto it = c.blocks.find(key);
-        if (it == c.blocks.end()) it = c.blocks.emplace(key, build()).first;
+        if (it == c.blocks.end()) {
+            if (B == 1 && n > ONE_COLUMN_NODES) {
+                c.one_col_steps += n_steps;
+                if (c.one_col_steps < 64 || n > 140000 + 100 * c.one_col_steps) return nullptr;
+            }
+            it = c.blocks.emplace(key, build()).first;
+        }
         return it->second->k ? it->second.get() : nullptr;
     };
     const int64_t one_tile = hm.d == 2 ? 2048 : 4096;
@@ -758,17 +832,20 @@ Blocks *plan_blocks(Ctx &c, int prec, const StepOp &op, int64_t n_cols, int B, i
     }
     const int npt_max = max_npt(prec, vec, W);
     const int cap = std::min(BL_FIELD / (vec * esz), 1024 * npt_max);
-    if (k < 64) {
+    // tiles whose regions fit by the estimate times f
+    auto fit = [&](double f) {
         double s = (double)n / tiles;
-        while (region_estimate(hm.d, s, k) > cap && s > 1) s *= 0.98;
-        tiles = std::max<int64_t>(1, (int64_t)std::ceil(n / s));
-    }
+        while (f * region_estimate(hm.d, s, k) > cap && s > 1) s *= 0.98;
+        return std::max<int64_t>(1, (int64_t)std::ceil(n / s));
+    };
+    // where the wished number does not fit, regions are up to a tenth larger than the estimate
+    if (k < 64 && region_estimate(hm.d, (double)n / tiles, k) > cap) tiles = fit(1.1);
     return lookup(false, tiles, [&] {
         std::shared_ptr<Blocks> b;
         int64_t tl = tiles;
         for (int tries = 0; tries < 8 && !b && n / tl >= 4; ++tries) {
             b = build_blocks(c, W, tl, k, cap, npt_max, vec * esz, esz);
-            tl += tl / 16 + 1;
+            tl = std::max(k < 64 ? fit(1.1) : 1, tl + tl / 16 + 1);
         }
         if (!b) b = std::make_shared<Blocks>();      // k = 0: no such regions
         b->vec = vec;
@@ -786,13 +863,13 @@ struct GroupLists {
 
 // Entries by (group, tile) in the given order; own: only the node's own tile (taps).
 template <typename Ent, typename AuxFn>
-GroupLists group_lists(const Blocks &B, int64_t groups, const std::vector<Ent> &ents,
-                       const std::vector<int32_t> &iperm, bool own, AuxFn aux) {
+GroupLists group_lists(Blocks &B, int64_t groups, const std::vector<Ent> &ents, const HostMesh &hm, bool own,
+                       AuxFn aux) {
     GroupLists L;
     L.ptr.assign(groups * B.n_tiles + 1, 0);
     auto each = [&](auto &&f) {
         for (const auto &e : ents) {
-            B.each_tile(iperm[e.node], [&](int64_t tile, int32_t loc, bool is_own) {
+            B.each_tile(hm, hm.iperm[e.node], [&](int64_t tile, int32_t loc, bool is_own) {
                 if (!own || is_own) f(e, (int64_t)(e.col / B.vec) * B.n_tiles + tile, loc);
             });
         }
@@ -827,15 +904,15 @@ int64_t live_groups(const BatchRun &run, int vec) {
 
 template <typename T>
 bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
-    const Blocks &B = *run.blocks;
+    Blocks &B = *run.blocks;
     const int64_t n = c.hm.n;
     hipStream_t s = c.stream;
     const int64_t groups = live_groups(run, B.vec);
     // the kernels take 16 bytes of columns or one; the caller's fields hold run.B columns
     MGRT_REQUIRE((B.vec == 1 || B.vec == 16 / (int)sizeof(T)) && groups * B.vec <= run.B, MGRT_E_STATE,
                  "regions of another precision or batch width");
-    GroupLists ld = group_lists(B, groups, run.inj, c.hm.iperm, false, [](const Injection &e) { return e.sid; });
-    GroupLists tp = group_lists(B, groups, run.rec, c.hm.iperm, true, [](const Record &e) { return e.dst; });
+    GroupLists ld = group_lists(B, groups, run.inj, c.hm, false, [](const Injection &e) { return e.sid; });
+    GroupLists tp = group_lists(B, groups, run.rec, c.hm, true, [](const Record &e) { return e.dst; });
     // strips record histories (at 31-bit offsets) or the velocity field, not both
     if (B.nx > 0 && run.hist &&
         (run.d_vel_out || (int64_t)run.hist_nodes.size() * run.B * (int64_t)sizeof(T) >= (1ll << 30)))
@@ -886,7 +963,7 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
     a.groups = (int32_t)groups;
     // one-column runs of small meshes have always summed in this order (their traces are within
     // rounding of the one-step launches', and stay what they were)
-    a.beta_first = run.B == 1 && n <= 65536 && !run.hist && !run.d_vel_out && !run.d_acc;
+    a.beta_first = run.B == 1 && n <= ONE_COLUMN_NODES && !run.hist && !run.d_vel_out && !run.d_acc;
     a.ld_ptr = pack.at<int32_t>(lo[0]);
     a.ld_loc = pack.at<int32_t>(lo[1]);
     a.ld_col = pack.at<int32_t>(lo[2]);
@@ -1121,10 +1198,10 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
 
 }  // namespace
 
-bool blocks_hold(const Ctx &c, const Blocks &B, const BatchRun &run) {
+bool blocks_hold(const Ctx &c, Blocks &B, const BatchRun &run) {
     const int64_t g = live_groups(run, B.vec);
-    return group_lists(B, g, run.inj, c.hm.iperm, false, [](const Injection &e) { return e.sid; }).fits &&
-           group_lists(B, g, run.rec, c.hm.iperm, true, [](const Record &e) { return e.dst; }).fits;
+    return group_lists(B, g, run.inj, c.hm, false, [](const Injection &e) { return e.sid; }).fits &&
+           group_lists(B, g, run.rec, c.hm, true, [](const Record &e) { return e.dst; }).fits;
 }
 
 bool run_blocks(Ctx &c, StepOp &op, BatchRun &run) {
