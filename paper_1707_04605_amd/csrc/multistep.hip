@@ -1131,10 +1131,14 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
     int64_t l = 0;
     const int64_t kk = B.k;
     int64_t per = chunk ? chunk : run.B == 1 ? 64 * kk : 64;
-    int64_t odd = 0;                       // launches of a captured run, as steps() issues them
-    for (int64_t q = 0; q < per; ++odd) q += next_steps(q, per);
-    if (odd & 1) per *= 2;
-    const int64_t nrep = run.n_steps / per;
+    auto launches_of = [&](int64_t cnt) {
+        int64_t m = 0;
+        for (int64_t q = 0; q < cnt; ++m) q += next_steps(q, cnt);
+        return m;
+    };
+    if (launches_of(per) % 2) per *= 2;
+    // (twice the steps need not be twice the launches where no history chunk ends a launch)
+    const int64_t nrep = launches_of(per) % 2 ? 0 : run.n_steps / per;
     if (!(run.flags & MGRT_F_NO_GRAPH) && nrep >= 2) {
         hipGraph_t graph = nullptr;
         if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) == hipSuccess) {
