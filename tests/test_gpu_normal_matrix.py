@@ -1,7 +1,7 @@
 """TV solves on the formed normal matrix at the edges of its tiles: one block of 64 and its
-neighbours, odd and even numbers of blocks (the factor takes them in pairs), columns that leave
-a ragged tile of 64 and of 128, rows in one panel, in split sums and in whole tiles of 128, and
-a factor large enough for updates in tiles of 128."""
+neighbours, block rows that fill and leave groups of the factor, columns that leave a ragged tile of
+64 and of 128, and matrices large enough for tiles of 128 in the normal matrix (3,969 unknowns)
+and in the factor's updates (4,289)."""
 import numpy as np
 import pytest
 
@@ -38,3 +38,21 @@ def test_direct_solve(mgrt, M, rows, prec):
     err = float(np.linalg.norm(z[0] - ref) / np.linalg.norm(ref))
     print(f"M={M} rows={rows} fp{prec}: {err:.2e}")
     assert err <= 1e-9
+
+
+@pytest.mark.parametrize("M,rows,prec", [(3969, 5200, 32), (4289, 5600, 64), (4300, 5600, 32), (4353, 5700, 64)])
+def test_direct_solve_in_tiles_of_128(mgrt, M, rows, prec):
+    """One step where whole tiles of 128 and the quarters behind them meet a ragged edge, in the
+    normal matrix (all) and in the factor (from 4,289).  A Gaussian L with 1.3 M rows leaves the
+    matrix a condition number of about 250: 250 * 2^-53 * M <= 2e-10."""
+    rng = np.random.default_rng(M)
+    L = rng.normal(size=(rows, M))
+    if prec == 32:
+        L = L.astype(np.float32)
+    r = rng.normal(size=rows)
+    ref = tv.tv_iterates(L.astype(np.float64), r, np.eye(M), 0.5, 1)[0]
+    z, its = mgrt.Context(0).tv_invert_level(L, r, np.arange(M + 1), np.arange(M), np.ones(M), 0.5, iters=1)
+    assert its[0] == 0
+    err = float(np.linalg.norm(z[0] - ref) / np.linalg.norm(ref))
+    print(f"M={M} rows={rows} fp{prec}: {err:.2e}")
+    assert err <= 2e-10
