@@ -24,7 +24,6 @@
 #include <cmath>
 #include <cstdlib>
 #include <iterator>
-#include <map>
 #include <memory>
 #include <new>
 #include <system_error>
@@ -55,14 +54,14 @@ struct Blocks {
         int32_t tile, loc;
         bool own;
     };
-    // places of the nodes that carried loads or taps so far
-    std::map<int32_t, std::vector<Place>> places;
+    // places of the nodes that carried loads or taps so far; place_at[node]: where, or -1
+    std::vector<std::vector<Place>> places;
+    std::vector<int32_t> place_at;
 
     // A tile updates the nodes within distance k - 1 of it, so the tiles that update node ii are
     // those of the nodes within distance k - 1 of ii.
     const std::vector<Place> &places_of(const HostMesh &hm, int32_t ii) {
-        const auto it = places.find(ii);
-        if (it != places.end()) return it->second;
+        if (place_at[ii] >= 0) return places[place_at[ii]];
         std::vector<int32_t> ball{ii}, seen{ii}, tiles;
         std::vector<Place> out;
         size_t f0 = 0;
@@ -91,7 +90,9 @@ struct Blocks {
             seen.swap(all);
             f0 = f1;
         }
-        return places.emplace(ii, std::move(out)).first->second;
+        places.push_back(std::move(out));
+        place_at[ii] = (int32_t)places.size() - 1;
+        return places.back();
     }
 
     // f(tile, local entry, own) for every tile that updates node ii
@@ -598,6 +599,7 @@ std::shared_ptr<Blocks> build_blocks(Ctx &c, int W, int64_t n_tiles, int k, int 
     B->W = W;
     B->n_tiles = n_tiles;
     B->tile_of.resize(n);
+    B->place_at.assign(n, -1);
     B->h_cnt.assign((size_t)n_tiles * (k + 1), 0);
     B->ents.resize(n_tiles);
     std::vector<std::vector<uint16_t>> nbs(n_tiles);       // [entry][W]: LDS byte offsets

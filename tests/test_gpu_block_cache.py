@@ -71,3 +71,32 @@ def test_budget_bounds_what_waits(mgrt, work):
     assert f0 - free() > 1.5 * GB
     ctx.misfit_gradient(*args, precision=32, mem_budget_gb=0.5)
     assert f0 - free() < 0.5 * GB + GB // 4
+
+
+def test_two_threads_share_blocks(mgrt, work):
+    """Two contexts on two threads give and take blocks while the other one runs, captures and
+    replays: the same results as one after the other."""
+    import threading
+    p, args = work
+    q = configs.make("c1", N=260, L=0, n_src=32, n_steps=600)
+    a, b = mgrt.context_for_problem(p), mgrt.context_for_problem(q)
+
+    def gradients():
+        return [a.misfit_gradient(*args, precision=32) for _ in range(3)]
+
+    def forwards():
+        return [b.forward_traces(q.src, q.rec, q.wavelet, q.dt, q.n_steps, precision=prec)
+                for prec in (32, 64, 32, 64)]
+
+    ref = gradients(), forwards()
+    got = [None, None]
+
+    def run(i, fn):
+        got[i] = fn()
+    threads = [threading.Thread(target=run, args=(i, fn)) for i, fn in enumerate((gradients, forwards))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for x, y in zip(ref, got):
+        assert y is not None and all(np.array_equal(u, v) for u, v in zip(x, y))
