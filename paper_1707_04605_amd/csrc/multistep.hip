@@ -54,40 +54,42 @@ struct Blocks {
         int32_t tile, loc;
         bool own;
     };
-    // places of the nodes that carried loads or taps so far; place_at[node]: where, or -1
+    // places of the nodes that carried loads so far; place_at[node]: where, or -1
     std::vector<std::vector<Place>> places;
-    std::vector<int32_t> place_at;
+    std::vector<int32_t> place_at, seen;             // seen[node]: the last search that met it
+    int32_t searches = 0;
+
+    // node ii among the entries at distance d of tile t (ascending)
+    Place place(int32_t ii, int32_t t, int d) const {
+        const int32_t *ct = &h_cnt[(size_t)t * (k + 1)];
+        const auto e = ents[t].begin();
+        return Place{t, (int32_t)(std::lower_bound(e + (d ? ct[d - 1] : 0), e + ct[d], ii) - e), d == 0};
+    }
 
     // A tile updates the nodes within distance k - 1 of it, so the tiles that update node ii are
     // those of the nodes within distance k - 1 of ii.
     const std::vector<Place> &places_of(const HostMesh &hm, int32_t ii) {
         if (place_at[ii] >= 0) return places[place_at[ii]];
-        std::vector<int32_t> ball{ii}, seen{ii}, tiles;
+        std::vector<int32_t> ball{ii}, tiles;
         std::vector<Place> out;
+        seen[ii] = ++searches;
         size_t f0 = 0;
-        for (int d = 0; d < k; ++d) {
+        for (int d = 0; d < (n_tiles == 1 ? 1 : k); ++d) {
             const size_t f1 = ball.size();
             for (size_t f = f0; f < f1; ++f) {
                 const int32_t t = tile_of[ball[f]];
-                if (std::find(tiles.begin(), tiles.end(), t) != tiles.end()) continue;
-                tiles.push_back(t);
-                // the entries at distance d of the tile, ascending
-                const int32_t *ct = &h_cnt[(size_t)t * (k + 1)];
-                const auto e0 = ents[t].begin() + (d ? ct[d - 1] : 0), e1 = ents[t].begin() + ct[d];
-                out.push_back(Place{t, (int32_t)(std::lower_bound(e0, e1, ii) - ents[t].begin()), d == 0});
-            }
-            if (n_tiles == 1) break;
-            std::vector<int32_t> next;
-            for (size_t f = f0; f < f1; ++f) {
+                if (std::find(tiles.begin(), tiles.end(), t) == tiles.end()) {
+                    tiles.push_back(t);
+                    out.push_back(place(ii, t, d));
+                }
                 const int64_t i = hm.perm[ball[f]];
-                for (int64_t q = hm.krow[i]; q < hm.krow[i + 1]; ++q) next.push_back(hm.iperm[hm.kcol[q]]);
+                for (int64_t q = hm.krow[i]; q < hm.krow[i + 1]; ++q) {
+                    const int32_t jj = hm.iperm[hm.kcol[q]];
+                    if (seen[jj] == searches) continue;
+                    seen[jj] = searches;
+                    ball.push_back(jj);
+                }
             }
-            std::sort(next.begin(), next.end());
-            next.erase(std::unique(next.begin(), next.end()), next.end());
-            std::vector<int32_t> all;
-            std::set_difference(next.begin(), next.end(), seen.begin(), seen.end(), std::back_inserter(ball));
-            std::set_union(seen.begin(), seen.end(), next.begin(), next.end(), std::back_inserter(all));
-            seen.swap(all);
             f0 = f1;
         }
         places.push_back(std::move(out));
@@ -95,21 +97,31 @@ struct Blocks {
         return places.back();
     }
 
-    // f(tile, local entry, own) for every tile that updates node ii
+    // f(tile, local entry) for every tile that updates node ii, or for the node's own alone
     template <typename F>
-    void each_tile(const HostMesh &hm, int32_t ii, F &&f) {
+    void each_tile(const HostMesh &hm, int32_t ii, bool own, F &&f) {
         if (nx == 0) {
-            for (const Place &q : places_of(hm, ii)) f((int64_t)q.tile, q.loc, q.own);
+            if (own) {
+                const Place q = place(ii, tile_of[ii], 0);
+                f((int64_t)q.tile, q.loc);
+            } else {
+                for (const Place &q : places_of(hm, ii)) f((int64_t)q.tile, q.loc);
+            }
             return;
         }
+        // chunks of rows and strips about the node
         const int64_t x = ii % nx, y = ii / nx;
-        for (int64_t cy = 0; cy < chunks; ++cy) {
+        const int64_t c0 = std::max<int64_t>(0, std::max<int64_t>(0, y - k) * chunks / ny - 1);
+        const int64_t c1 = std::min(chunks, (y + k) * chunks / ny + 2);
+        const int64_t s0 = std::max<int64_t>(0, std::max<int64_t>(0, x + k - 64) * strips / nx - 1);
+        const int64_t s1 = std::min(strips, (x + k) * strips / nx + 2);
+        for (int64_t cy = c0; cy < c1; ++cy) {
             const int64_t ya = ny * cy / chunks, yb = ny * (cy + 1) / chunks;
-            if (y < ya - k || y >= yb + k) continue;
-            for (int64_t sx = 0; sx < strips; ++sx) {
+            if (own ? y < ya || y >= yb : y < ya - k || y >= yb + k) continue;
+            for (int64_t sx = s0; sx < s1; ++sx) {
                 const int64_t xa = nx * sx / strips, xb = nx * (sx + 1) / strips;
-                if (x < xa - k || x >= xa - k + 64) continue;
-                f(cy * strips + sx, (int32_t)((y - ya + k) * 64 + (x - xa + k)), x >= xa && x < xb && y >= ya && y < yb);
+                if (own ? x < xa || x >= xb : x < xa - k || x >= xa - k + 64) continue;
+                f(cy * strips + sx, (int32_t)((y - ya + k) * 64 + (x - xa + k)));
             }
         }
     }
@@ -600,6 +612,7 @@ std::shared_ptr<Blocks> build_blocks(Ctx &c, int W, int64_t n_tiles, int k, int 
     B->n_tiles = n_tiles;
     B->tile_of.resize(n);
     B->place_at.assign(n, -1);
+    B->seen.assign(n, 0);
     B->h_cnt.assign((size_t)n_tiles * (k + 1), 0);
     B->ents.resize(n_tiles);
     std::vector<std::vector<uint16_t>> nbs(n_tiles);       // [entry][W]: LDS byte offsets
@@ -863,31 +876,35 @@ struct GroupLists {
     bool fits = true;
 };
 
-// Entries by (group, tile) in the given order; own: only the node's own tile (taps).
+// Entries by (group, tile) in the given order; own: only the node's own tile (taps).  Lists that
+// overflow by the nodes' own tiles alone are given up before any other tile is looked for.
 template <typename Ent, typename AuxFn>
 GroupLists group_lists(Blocks &B, int64_t groups, const std::vector<Ent> &ents, const HostMesh &hm, bool own,
                        AuxFn aux) {
     GroupLists L;
-    L.ptr.assign(groups * B.n_tiles + 1, 0);
-    auto each = [&](auto &&f) {
-        for (const auto &e : ents) {
-            B.each_tile(hm, hm.iperm[e.node], [&](int64_t tile, int32_t loc, bool is_own) {
-                if (!own || is_own) f(e, (int64_t)(e.col / B.vec) * B.n_tiles + tile, loc);
+    auto each = [&](bool own_tile, auto &&f) {
+        for (const auto &e : ents)
+            B.each_tile(hm, hm.iperm[e.node], own_tile, [&](int64_t tile, int32_t loc) {
+                f(e, (int64_t)(e.col / B.vec) * B.n_tiles + tile, loc);
             });
-        }
     };
-    each([&](const Ent &, int64_t li, int32_t) { L.ptr[li + 1]++; });
-    for (size_t i = 0; i + 1 < L.ptr.size(); ++i) {
-        if (L.ptr[i + 1] > BL_CAP) L.fits = false;
-        L.ptr[i + 1] += L.ptr[i];
-    }
+    auto count = [&](bool own_tile) {
+        L.ptr.assign(groups * B.n_tiles + 1, 0);
+        each(own_tile, [&](const Ent &, int64_t li, int32_t) {
+            if (++L.ptr[li + 1] > BL_CAP) L.fits = false;
+        });
+    };
+    count(true);
+    if (L.fits && !own) count(false);
+    if (!L.fits) return L;
+    for (size_t i = 0; i + 1 < L.ptr.size(); ++i) L.ptr[i + 1] += L.ptr[i];
     const size_t ne = std::max<size_t>(1, L.ptr.back());
     L.loc.assign(ne, 0);
     L.col.assign(ne, 0);
     L.aux.assign(ne, 0);
     L.w.assign(ne, 0.0);
     std::vector<int32_t> fill(L.ptr.begin(), L.ptr.end() - 1);
-    each([&](const Ent &e, int64_t li, int32_t loc) {
+    each(own, [&](const Ent &e, int64_t li, int32_t loc) {
         const int32_t q = fill[li]++;
         L.loc[q] = loc;
         L.col[q] = e.col % B.vec;
@@ -913,13 +930,14 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
     // the kernels take 16 bytes of columns or one; the caller's fields hold run.B columns
     MGRT_REQUIRE((B.vec == 1 || B.vec == 16 / (int)sizeof(T)) && groups * B.vec <= run.B, MGRT_E_STATE,
                  "regions of another precision or batch width");
-    GroupLists ld = group_lists(B, groups, run.inj, c.hm, false, [](const Injection &e) { return e.sid; });
     GroupLists tp = group_lists(B, groups, run.rec, c.hm, true, [](const Record &e) { return e.dst; });
+    if (!tp.fits) return false;
+    GroupLists ld = group_lists(B, groups, run.inj, c.hm, false, [](const Injection &e) { return e.sid; });
+    if (!ld.fits) return false;
     // strips record histories (at 31-bit offsets) or the velocity field, not both
     if (B.nx > 0 && run.hist &&
         (run.d_vel_out || (int64_t)run.hist_nodes.size() * run.B * (int64_t)sizeof(T) >= (1ll << 30)))
         return false;
-    if (!ld.fits || !tp.fits) return false;
     if (run.d_series == nullptr) MGRT_REQUIRE(run.inj.empty(), MGRT_E_ARG, "loads without series");
     Pack pack;
     size_t lo[5], to[5];

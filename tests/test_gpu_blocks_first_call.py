@@ -45,3 +45,19 @@ def test_points_that_move(mgrt, cfg, N, src):
         y = ctx.forward_traces(*args, precision=32)
         assert ctx.last_timing()["steps_per_launch"] > 1
         assert np.array_equal(y, ctx.forward_traces(*args, precision=32, one_step=True))
+
+
+def test_more_loads_than_a_tile_holds(mgrt):
+    """Residuals of 30 receivers in one place: both sweeps take one launch per step, also where
+    the forward sweep alone would not have to, with the values of a requested batch width."""
+    p = configs.make("c1", N=60, L=0, n_src=4, n_steps=260)
+    rec = np.repeat(p.rec[:, :1], 30, axis=1)
+    res = np.random.default_rng(4).standard_normal((4, 30, p.n_steps))
+    ctx = mgrt.context_for_problem(p)
+    args = (p.src, rec, p.wavelet, p.dt, p.n_steps, res, "fine")
+    a = ctx.misfit_gradient(*args, precision=64)
+    t = ctx.last_timing()
+    assert t["steps_per_launch"] == 1
+    b = ctx.misfit_gradient(*args, precision=64, batch=t["batch"])
+    # the same steps: equal but for the order in which a node adds up its columns
+    assert float(np.linalg.norm(a - b) / np.linalg.norm(b)) <= 1e-12
