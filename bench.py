@@ -33,6 +33,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
+# wave instructions of the vector ALUs: 256 CUs x 4 SIMDs, one of 64 lanes in 4 cycles at 2.4 GHz
+VALU_PEAK_GINST = 256 * 4 * 2.4 / 4
 LEGS_DEFAULT = ["direct", "fp64", "plain", "jacobian", "c1", "c4", "c5"]
 
 
@@ -47,28 +49,40 @@ def step_kernel_bytes(n, nnz_off, B, esz):
     return 3 * esz * n * B + nnz_off * (4 + esz) + esz * n
 
 
-def kernel_source_hash():
-    """Hash of the stepping kernels' source (the device code and its launch mapping);
-    host-side changes (tuning, graph replay, shared host structures) leave it alone."""
-    h = hashlib.sha256()
-    for f in ("step_kernels.hpp",):
-        h.update(open(os.path.join(ROOT, "paper_1707_04605_amd", "csrc", f), "rb").read())
-    return h.hexdigest()[:16]
+def kernel_source_hash(name="step_kernels.hpp"):
+    """Hash of a stepping kernel's source (for the one-step launches the device code and its
+    launch mapping); host-side changes (tuning, graph replay, shared host structures) leave
+    it alone."""
+    src = open(os.path.join(ROOT, "paper_1707_04605_amd", "csrc", name), "rb").read()
+    return hashlib.sha256(src).hexdigest()[:16]
+
+
+def counter_summary(name, source="step_kernels.hpp"):
+    """Text of a committed counter summary if it was taken on the current source, else None."""
+    path = os.path.join(ROOT, "profiles", name)
+    if not os.path.exists(path):
+        return None
+    txt = open(path).read()
+    m = re.search(r"kernel_source_hash:\s*(\w+)", txt)
+    return txt if m and m.group(1) == kernel_source_hash(source) else None
 
 
 def traffic_from_profile(name, batch, variant):
     """HBM bytes per launch measured with rocprofv3 counters for this batch width and
     launch variant, if the committed summary was taken on the current kernel source;
     else None."""
-    path = os.path.join(ROOT, "profiles", name)
-    if not os.path.exists(path):
-        return None
-    txt = open(path).read()
-    m = re.search(r"kernel_source_hash:\s*(\w+)", txt)
-    if not m or m.group(1) != kernel_source_hash():
-        return None
-    t = re.search(rf"hbm_bytes_per_launch_b{int(batch)}_v{int(variant)}:\s*([0-9.eE+]+)", txt)
+    txt = counter_summary(name)
+    t = txt and re.search(rf"hbm_bytes_per_launch_b{int(batch)}_v{int(variant)}:\s*([0-9.eE+]+)", txt)
     return float(t.group(1)) if t else None
+
+
+def strips_from_profile(key):
+    """(HBM bytes, VALU wave instructions) per launch of several steps on strips, for the key
+    `outputs_precision_nodes_batch` of the committed counter summary; (None, None) if it has none."""
+    txt = counter_summary("multistep_counters.md", "strips.hpp")
+    v = [txt and re.search(rf"{what}_per_launch_{key}:\s*([0-9.eE+]+)", txt)
+         for what in ("hbm_bytes", "valu_instructions")]
+    return tuple(float(m.group(1)) if m else None for m in v)
 
 
 def tuning(ctx):
@@ -78,11 +92,15 @@ def tuning(ctx):
     return [round(x, 1) for x in t] if any(t) else None
 
 
-def roofline(tm, n, esz, launches_ms, launches, counter_file=None, tune=None):
-    """Stepping-kernel roofline: the library's algorithmic bytes of the last call's
-    launches (which include velocity and accumulator traffic of adjoint sweeps) over the
-    event-timed launch duration."""
-    B = tm["batch"]
+def roofline(tm, n, esz, launches_ms, launches, counter_file=None, tune=None, strips=None):
+    """Stepping-kernel roofline: the library's algorithmic bytes of the last call's launches
+    (which include velocity and accumulator traffic of adjoint sweeps) over the event-timed
+    launch duration.  Launches of several steps move far fewer bytes per step than HBM could:
+    where the committed counters hold their VALU instructions, those over the duration are the
+    achieved rate and the HBM figures stand beside it; elsewhere the chain of sub-steps
+    bounds them and the HBM fraction only says how little of it is used."""
+    B, k = tm["batch"], max(1, tm["steps_per_launch"])
+    prec = "FP32" if esz == 4 else "FP64"
     nnz_off = int(round(tm["ell_mean_width"] * n))
     launch_bytes = step_kernel_bytes(n, nnz_off, B, esz)
     if tm.get("step_bytes", 0) > 0 and tm["step_launches"] > 0:
@@ -92,23 +110,33 @@ def roofline(tm, n, esz, launches_ms, launches, counter_file=None, tune=None):
     # the per-entry operator count (3 state words + stiffness row with one value per
     # entry + two diagonal coefficients, over B), for comparison
     entry_bytes = step_kernel_bytes(n, nnz_off, B, esz) + esz * n
-    per_entry_s = avg_launch_s / max(1, tm["steps_per_launch"])
-    return {"bound": "hbm" if tm["steps_per_launch"] <= 1 else "valu", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": achieved / HBM_PEAK_GBS,
-            "traffic": (traffic_from_profile(counter_file, B, tm["variant"])
-                        if counter_file and tm["steps_per_launch"] <= 1 else None),
-            "kernel": (f"{tm['steps_per_launch']} steps per launch (B={B}, {'FP32' if esz == 4 else 'FP64'})"
-                       if tm["steps_per_launch"] > 1 else
-                       f"k_step (B={B}, {'FP32' if esz == 4 else 'FP64'}, variant {tm['variant']})"),
-            "bytes_per_launch": launch_bytes, "avg_launch_us": avg_launch_s * 1e6,
-            "avg_launch_timing": ("HIP events on the library's stream around the replayed "
-                                  "step graphs (and around each direct launch): kernel time "
-                                  "plus the gaps between graph nodes, so at or above the "
-                                  "profiler's kernel average"),
-            "per_entry_bytes_per_launch": entry_bytes,
-            "per_entry_frac": entry_bytes / per_entry_s / 1e9 / HBM_PEAK_GBS,
-            "bytes_per_node_update": launch_bytes / (n * B) / max(1, tm["steps_per_launch"]),
-            "launch_variant_tuning_us": tune}
+    per_entry_s = avg_launch_s / k
+    hbm = {"achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
+           "traffic": None}
+    rf = {"bound": "hbm", **hbm,
+          "kernel": f"k_step (B={B}, {prec}, variant {tm['variant']})",
+          "bytes_per_launch": launch_bytes, "avg_launch_us": avg_launch_s * 1e6,
+          "avg_launch_timing": ("HIP events on the library's stream around the replayed "
+                                "step graphs (and around each direct launch): kernel time "
+                                "plus the gaps between graph nodes, so at or above the "
+                                "profiler's kernel average"),
+          "per_entry_bytes_per_launch": entry_bytes,
+          "per_entry_frac": entry_bytes / per_entry_s / 1e9 / HBM_PEAK_GBS,
+          "bytes_per_node_update": launch_bytes / (n * B) / k,
+          "launch_variant_tuning_us": tune}
+    if k == 1:
+        if counter_file:
+            rf["traffic"] = traffic_from_profile(counter_file, B, tm["variant"])
+        return rf
+    rf["kernel"] = f"{k} steps per launch (B={B}, {prec})"
+    rf["bound"] = "latency"
+    hbm["traffic"], valu = (strips_from_profile(f"{strips}_{prec.lower()}_n{n}_b{B}") if strips else (None, None))
+    rf["traffic"] = hbm["traffic"]
+    if valu:
+        rate = valu / avg_launch_s / 1e9
+        rf.update(bound="valu", achieved=rate, peak=VALU_PEAK_GINST, unit="1e9 wave instructions/s",
+                  frac=rate / VALU_PEAK_GINST, valu_instructions_per_launch=valu, hbm=hbm)
+    return rf
 
 
 def base_result(args, metric, value, unit, ms_per_step, dtype, config):
@@ -210,14 +238,14 @@ def bench_c2(args):
     updates = n * n_steps * n_src
     value = updates / wall
     log(f"fp32: {1e3 * wall:.1f} ms per call, {value:.3e} node-updates/s, batch {tm['batch']}, "
-        f"{tm['graph_steps']} of {tm['step_launches']} steps replayed")
+        f"{tm['graph_steps']} of {n_steps * -(-n_src // tm['batch'])} steps replayed")
     result = base_result(
         args, "node-updates/s x sources (FP32 leap-frog, 2D batched)", value, "node-updates/s",
         1e3 * wall, "f32",
         {"workload": "2D batched forward: 1024^2 cells (1,050,625 nodes), 64 monostatic "
                      "sources, 16,000 steps, lumped mass, absorbing boundary",
          "nodes": n, "sources": n_src, "leapfrog_steps": n_steps, "batch": tm["batch"]})
-    result["roofline"] = roofline(tm, n, 4, ms, launches, "step_fp32_c2_counters.md", tune)
+    result["roofline"] = roofline(tm, n, 4, ms, launches, "step_fp32_c2_counters.md", tune, "traces")
     result["batch_tuning"] = tm["batch_tuning"]
     result["mall_note"] = mall_note(n, tm, 4)
     if "direct" in legs:
@@ -238,7 +266,7 @@ def bench_c2(args):
 
     if "fp64" in legs:
         _, w64, ms64, l64, tm64, _ = measure_forward(ctx, p, args, 64, n_steps, warmup=1, steps=1)
-        rf64 = roofline(tm64, n, 8, ms64, l64, "step_fp64_c2_counters.md")
+        rf64 = roofline(tm64, n, 8, ms64, l64, "step_fp64_c2_counters.md", strips="traces")
         result["fp64"] = {"value": updates / w64, "unit": "node-updates/s",
                           "ms_per_call": 1e3 * w64, "batch": tm64["batch"],
                           "batch_tuning": tm64["batch_tuning"], "roofline": rf64,
@@ -337,11 +365,13 @@ def cpu_other_configs():
 
 
 def mall_note(n, tm, esz):
-    """Whether one batch's working set (the two state fields and the per-node operator
+    """Whether one batch's working set (its state fields and the per-node operator
     records) fits the 256 MB Infinity Cache, so that the roofline's HBM fraction may count
     traffic the cache serves."""
-    ws = 2 * n * tm["batch"] * esz + (tm["step_bytes"] / tm["step_launches"]
-                                      - 3 * n * tm["batch"] * esz if tm["step_launches"] else 0)
+    # one pair of fields, three words a launch; several steps a launch: two pairs, four words
+    fields, words = (2, 3) if tm["steps_per_launch"] <= 1 else (4, 4)
+    ws = fields * n * tm["batch"] * esz + (tm["step_bytes"] / tm["step_launches"]
+                                           - words * n * tm["batch"] * esz if tm["step_launches"] else 0)
     return {"working_set_bytes": ws, "infinity_cache_bytes": 256 << 20,
             "fits": bool(ws <= (256 << 20))}
 
@@ -564,7 +594,8 @@ def jacobian_tv_legs(ctx, p, args, y_true, deconv):
         "stepping_s": step_s, "stepping_launches": tm["step_launches"],
         "workload": "multigrid Jacobian, 1024^2 cells, 64 sources x 512 samples, 64^2 coarse "
                     "level (8,192 columns), 16,000 steps, FP32 fields, FP64 sums",
-        "roofline": roofline(tm, n, 4, tm["step_ms_total"], tm["step_launches"], tune=tune)}
+        "roofline": roofline(tm, n, 4, tm["step_ms_total"], tm["step_launches"], tune=tune,
+                             strips="histories")}
     if deconv:
         dec = []
         nJ = float(torch.linalg.norm(J))
