@@ -13,9 +13,13 @@ namespace mgrt {
 // Device blocks between calls.  Bounded (CACHE_BYTES per device, and the memory budget of a call
 // that has one), shared by all contexts of a device under a mutex, given back on request, when an
 // allocation fails and when a context of the device is destroyed.  A block enters only after
-// the device is idle, as hipFree would wait, so that no kernel of another stream still uses it.
+// its context's stream is idle (side streams are joined before their buffers go), so that no
+// kernel still uses it: hipFree waits for the device, and hipDeviceSynchronize would invalidate a
+// capture that another thread has open.
 // Nothing here throws: blocks are given and taken in destructors and at the C entries.
 namespace {
+
+thread_local hipStream_t call_stream = nullptr;
 
 constexpr size_t CACHE_MIN = 1 << 20;             // smaller blocks: hipMalloc takes about 1 us
 constexpr int CACHE_DEVICES = 64;
@@ -36,6 +40,15 @@ BlockCache *block_cache() {
 }
 
 }  // namespace
+
+CallStream::CallStream(hipStream_t s) : before(call_stream) { call_stream = s; }
+CallStream::~CallStream() { call_stream = before; }
+
+// never destroyed, as the block cache
+std::shared_mutex &capture_mutex() {
+    static std::shared_mutex *m = new std::shared_mutex;
+    return *m;
+}
 
 void *cache_take(size_t bytes, size_t *got) noexcept {
     BlockCache *c = bytes >= CACHE_MIN ? block_cache() : nullptr;
@@ -58,7 +71,7 @@ bool cache_give(void *p, size_t bytes, int device) noexcept {
     int cur = -1;
     if (bytes < CACHE_MIN || bytes > CACHE_BYTES || hipGetDevice(&cur) != hipSuccess || cur != device) return false;
     BlockCache *c = block_cache();
-    if (!c || hipDeviceSynchronize() != hipSuccess) return false;
+    if (!c || !call_stream || hipStreamSynchronize(call_stream) != hipSuccess) return false;
     (void)cache_trim(CACHE_BYTES - bytes);            // the oldest make room
     std::lock_guard<std::mutex> lk(c->mu);
     if (c->contexts == 0 || c->bytes + bytes > CACHE_BYTES) return false;
@@ -192,7 +205,7 @@ static std::vector<double> forward_impl(Ctx &c, const Acquisition &aq, const dou
                     rec.push_back(Record{aq.rec[s * aq.n_rec + r].node[a], 0, r * V + a,
                                          aq.rec[s * aq.n_rec + r].w[a]});
             run_plain(c, dt, n_steps, aq.src[s], g.data(), rec, parts.as<double>(), n_parts, flags);
-            MGRT_HIP(hipMemcpy(hp.data(), parts.p, hp.size() * sizeof(double), hipMemcpyDeviceToHost));
+            MGRT_HIP(copy_blocking(hp.data(), parts.p, hp.size() * sizeof(double), hipMemcpyDeviceToHost));
             for (int r = 0; r < aq.n_rec; ++r)
                 for (int64_t l = 0; l < n_steps; ++l) {
                     double t = 0;
@@ -240,7 +253,7 @@ static std::vector<double> forward_impl(Ctx &c, const Acquisition &aq, const dou
             run.d_pm = bufB.p;
             run.blocks = blocks;
             run_batch(c, op, run);
-            MGRT_HIP(hipMemcpy(hp.data(), parts.p, hp.size() * sizeof(double), hipMemcpyDeviceToHost));
+            MGRT_HIP(copy_blocking(hp.data(), parts.p, hp.size() * sizeof(double), hipMemcpyDeviceToHost));
             for (int b = 0; b < nb; ++b)
                 for (int r = 0; r < aq.n_rec; ++r)
                     for (int64_t l = 0; l < n_steps; ++l) {
@@ -399,7 +412,7 @@ static void forward_noalloc(Ctx &c, const Acquisition &aq, const double *wavelet
         MGRT_HIP(hipStreamSynchronize(s));
     }
     int hbad = 0;
-    MGRT_HIP(hipMemcpy(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost));
+    MGRT_HIP(copy_blocking(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost));
     MGRT_REQUIRE(!hbad, MGRT_E_NONFINITE, "non-finite trace value (unstable run?)");
     c.timing.batch = B;
     c.timing.ell_width = op.wmax;
@@ -442,7 +455,10 @@ int mgrt_destroy(mgrt_ctx *ctx) {
     (void)hipStreamSynchronize(ctx->c.stream);
     bool own = ctx->c.own_stream;
     hipStream_t s = ctx->c.stream;
-    delete ctx;
+    {
+        const CallStream stream(s);
+        delete ctx;
+    }
     cache_contexts(-1);
     if (own) (void)hipStreamDestroy(s);
     return MGRT_OK;

@@ -84,10 +84,14 @@ void make_plans(FftPlan &fwd, FftPlan &inv, int L, int64_t batch, hipStream_t s)
     // the library allocates the plan's work area itself: when that fails, the blocks that wait
     // for later calls (which count as free memory) make room
     auto plan = [](FftPlan &p, auto &&make) {
-        hipfftResult r = make(&p.h);
+        auto locked = [&] {
+            std::shared_lock<std::shared_mutex> lk(capture_mutex());
+            return make(&p.h);
+        };
+        hipfftResult r = locked();
         if (r != HIPFFT_SUCCESS && cache_trim(0)) {
             (void)hipGetLastError();
-            r = make(&p.h);
+            r = locked();
         }
         MGRT_FFT(r);
         p.live = true;

@@ -226,7 +226,7 @@ void gradient_t(Ctx &c, const Acquisition &aq, const std::vector<double> &g, dou
     MGRT_HIP(hipGetLastError());
     if (level == 1) {
         MGRT_HIP(hipStreamSynchronize(c.stream));
-        MGRT_HIP(hipMemcpy(grad, gf.p, (size_t)hm.m * 8, hipMemcpyDeviceToHost));
+        MGRT_HIP(copy_blocking(grad, gf.p, (size_t)hm.m * 8, hipMemcpyDeviceToHost));
     } else {
         DevBuf gc((size_t)hm.nc * 8);
         hipLaunchKernelGGL(k_grad_coarse, dim3((hm.nc + 3) / 4), dim3(256), 0, c.stream,
@@ -234,7 +234,7 @@ void gradient_t(Ctx &c, const Acquisition &aq, const std::vector<double> &g, dou
                            hm.nc, gc.as<double>());
         MGRT_HIP(hipGetLastError());
         MGRT_HIP(hipStreamSynchronize(c.stream));
-        MGRT_HIP(hipMemcpy(grad, gc.p, (size_t)hm.nc * 8, hipMemcpyDeviceToHost));
+        MGRT_HIP(copy_blocking(grad, gc.p, (size_t)hm.nc * 8, hipMemcpyDeviceToHost));
     }
     c.timing.batch = B;
     c.timing.node_updates = n * N * aq.n_src * (nseg > 1 ? 3 : 2);   // forward (twice), adjoint

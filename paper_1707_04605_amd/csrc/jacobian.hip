@@ -463,7 +463,7 @@ void jacobian_mg(Ctx &c, const Acquisition &aq, const std::vector<double> &g,
     }
     MGRT_HIP(hipGetLastError());
     MGRT_HIP(hipStreamSynchronize(c.stream));
-    MGRT_HIP(hipMemcpy(J_out, Jdev.p, (size_t)rows * M * 8,
+    MGRT_HIP(copy_blocking(J_out, Jdev.p, (size_t)rows * M * 8,
                        dev_out ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost));
     c.timing.batch = Bf;
 }
@@ -574,7 +574,7 @@ void jacobian_exact(Ctx &c, const Acquisition &aq, const std::vector<double> &g,
             tr.d_p = stA.p; tr.d_pm = stB.p;
             if (Bt == 1) tr.blocks = plan_blocks(c, prec, opt, 1, 1, N, opts);
             run_batch(c, opt, tr);
-            MGRT_HIP(hipMemcpy(hp.data(), parts.p, hp.size() * 8, hipMemcpyDeviceToHost));
+            MGRT_HIP(copy_blocking(hp.data(), parts.p, hp.size() * 8, hipMemcpyDeviceToHost));
             for (int q = 0; q < nt; ++q) {
                 const int64_t tl = t0 + q;
                 const int64_t s = s0 + tl / ncol;
@@ -588,7 +588,7 @@ void jacobian_exact(Ctx &c, const Acquisition &aq, const std::vector<double> &g,
             }
         }
     }
-    if (dev_out) MGRT_HIP(hipMemcpy(J_out, Jh.data(), Jh.size() * 8, hipMemcpyHostToDevice));
+    if (dev_out) MGRT_HIP(copy_blocking(J_out, Jh.data(), Jh.size() * 8, hipMemcpyHostToDevice));
     else std::memcpy(J_out, Jh.data(), Jh.size() * 8);
     c.timing.batch = Bt;
 }

@@ -10,6 +10,8 @@
 #include <tuple>
 #include <map>
 #include <memory>
+#include <mutex>
+#include <shared_mutex>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -35,6 +37,23 @@ struct Error : std::runtime_error {
     do {                                                                                  \
         if (!(cond)) throw ::mgrt::Error((code), (msg));                                  \
     } while (0)
+
+// A blocking copy (or an FFT plan) invalidates a stream capture that another thread has open, and
+// fails itself.  The library's captures hold this mutex alone, such calls share it.
+std::shared_mutex &capture_mutex();
+inline hipError_t copy_blocking(void *dst, const void *src, size_t bytes, hipMemcpyKind kind) {
+    std::shared_lock<std::shared_mutex> lk(capture_mutex());
+    return hipMemcpy(dst, src, bytes, kind);
+}
+
+// The stream of the context whose call this thread is in; null outside of calls.
+struct CallStream {
+    hipStream_t before;
+    explicit CallStream(hipStream_t s);
+    ~CallStream();
+    CallStream(const CallStream &) = delete;
+    CallStream &operator=(const CallStream &) = delete;
+};
 
 // Freed blocks of 1 MiB and more wait in a per-device cache (api.hip) for the next
 // allocation of about their size: once a process has allocated and freed about the device's
@@ -139,7 +158,7 @@ struct Arena {
 template <typename T>
 inline T *put(Arena &ar, const std::vector<T> &v) {
     T *p = static_cast<T *>(ar.take(std::max<size_t>(1, v.size()) * sizeof(T)));
-    if (!v.empty()) MGRT_HIP(hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
+    if (!v.empty()) MGRT_HIP(copy_blocking(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
     return p;
 }
 
@@ -148,7 +167,7 @@ inline DevBuf upload(const T *v, size_t count, hipStream_t s) {
     // blocking copy: the host array may be freed as soon as this returns
     (void)s;
     DevBuf b(count * sizeof(T));
-    if (count) MGRT_HIP(hipMemcpy(b.p, v, count * sizeof(T), hipMemcpyHostToDevice));
+    if (count) MGRT_HIP(copy_blocking(b.p, v, count * sizeof(T), hipMemcpyHostToDevice));
     return b;
 }
 template <typename T>
@@ -179,7 +198,7 @@ struct Pack {
             own.alloc(b);
             dev = own.as<char>();
         }
-        MGRT_HIP(hipMemcpy(dev, h.data(), b, hipMemcpyHostToDevice));
+        MGRT_HIP(copy_blocking(dev, h.data(), b, hipMemcpyHostToDevice));
     }
     template <typename T> T *at(size_t off) const { return reinterpret_cast<T *>(dev + off); }
 };
@@ -327,6 +346,13 @@ struct Ctx {
     int64_t grid_nx = -1;              // row length of a lexicographic 2D grid, 0: none, -1: not looked at
     std::shared_ptr<void> fft_plans;   // deconv.hip: FFT plans kept per (length, batch, precision)
     mgrt_timing timing{};
+    hipStream_t capture_stream = nullptr;   // runs of steps are captured here, never run (capture_launches)
+    Ctx() = default;
+    Ctx(const Ctx &) = delete;
+    Ctx &operator=(const Ctx &) = delete;
+    ~Ctx() {
+        if (capture_stream) (void)hipStreamDestroy(capture_stream);
+    }
 };
 
 // mesh_ops.hip
@@ -403,6 +429,9 @@ struct BatchRun {
                                                     // takes one launch per step)
 };
 int64_t pml_entries(const Ctx &c);
+// step.hip: a graph of what launches puts on the stream it is given, an even number of buffer
+// swaps; null where it could not be captured (nothing ran: launch directly).
+hipGraphExec_t capture_launches(Ctx &c, const std::function<void(hipStream_t)> &launches);
 // multistep.hip: the regions for runs of n_cols columns at batch width B in a call of
 // n_steps steps (null: one launch per step).  The state, velocity and PML layout of a run
 // differs between the two, so runs that hand a state on all take one or the other.
@@ -453,6 +482,7 @@ struct mgrt_ctx {
 template <typename F>
 static inline int mgrt_guarded(mgrt_ctx *ctx, F &&f) {
     if (!ctx) return MGRT_E_ARG;
+    const mgrt::CallStream stream(ctx->c.stream);
     try {
         MGRT_HIP(hipSetDevice(ctx->c.device));
         f(ctx->c);

@@ -23,10 +23,8 @@
 #include <atomic>
 #include <cmath>
 #include <cstdlib>
-#include <iterator>
 #include <memory>
 #include <new>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -49,10 +47,9 @@ struct Blocks {
     // strips instead of regions (strips.hpp): nx > 0, tiles are strips x chunks of rows
     int64_t nx = 0, ny = 0, strips = 0, chunks = 0;
 
-    // where a region updates a node: its tile, the local entry, whether the tile is the node's own
+    // where a region updates a node
     struct Place {
         int32_t tile, loc;
-        bool own;
     };
     // places of the nodes that carried loads so far; place_at[node]: where, or -1
     std::vector<std::vector<Place>> places;
@@ -63,7 +60,7 @@ struct Blocks {
     Place place(int32_t ii, int32_t t, int d) const {
         const int32_t *ct = &h_cnt[(size_t)t * (k + 1)];
         const auto e = ents[t].begin();
-        return Place{t, (int32_t)(std::lower_bound(e + (d ? ct[d - 1] : 0), e + ct[d], ii) - e), d == 0};
+        return Place{t, (int32_t)(std::lower_bound(e + (d ? ct[d - 1] : 0), e + ct[d], ii) - e)};
     }
 
     // A tile updates the nodes within distance k - 1 of it, so the tiles that update node ii are
@@ -558,7 +555,7 @@ void bisect(NodeAt<D> *nodes, int64_t lo, int64_t hi, int64_t nt, int64_t t0, in
     if (depth < 4 && hi - lo > 2048) {
         try {
             half = std::thread([=] { bisect<D>(nodes, lo, mid, nl, t0, first, depth + 1); });
-        } catch (const std::system_error &) {       // no thread to be had: this one does both
+        } catch (...) {       // no thread to be had: this one does both
         }
     }
     if (!half.joinable()) bisect<D>(nodes, lo, mid, nl, t0, first, depth + 1);
@@ -1160,21 +1157,14 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
     // (twice the steps need not be twice the launches where no history chunk ends a launch)
     const int64_t nrep = launches_of(per) % 2 ? 0 : run.n_steps / per;
     if (!(run.flags & MGRT_F_NO_GRAPH) && nrep >= 2) {
-        hipGraph_t graph = nullptr;
-        if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) == hipSuccess) {
-            try {
-                steps(per);
-            } catch (...) {
-                hipGraph_t g2 = nullptr;
-                (void)hipStreamEndCapture(s, &g2);
-                if (g2) (void)hipGraphDestroy(g2);
-                throw;
-            }
-            MGRT_HIP(hipStreamEndCapture(s, &graph));
-            hipGraphExec_t exec = nullptr;
-            const hipError_t ie = hipGraphInstantiateWithFlags(&exec, graph, 0);
-            (void)hipGraphDestroy(graph);
-            MGRT_HIP(ie);
+        const hipGraphExec_t exec = capture_launches(c, [&](hipStream_t cs) {
+            s = L.s = cs;
+            steps(per);
+            s = L.s = c.stream;
+        });
+        if (!exec) {
+            launches = 0;
+        } else {
             launches *= nrep;
             hipError_t le = hipSuccess;
             for (int64_t r = 0; r < nrep && le == hipSuccess; ++r) le = hipGraphLaunch(exec, s);
@@ -1184,8 +1174,6 @@ bool run_blocks_t(Ctx &c, StepOp &op, BatchRun &run) {
             MGRT_HIP(se);
             l = nrep * per;
             c.timing.graph_steps += l;
-        } else {
-            (void)hipGetLastError();
         }
     }
     if (l < run.n_steps) steps(run.n_steps - l);

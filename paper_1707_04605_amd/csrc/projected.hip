@@ -202,7 +202,7 @@ extern "C" int mgrt_project_rows(mgrt_ctx *ctx, int64_t n_traces, int32_t n_samp
         const void *Jd = J;
         if (!J_on_device) {
             Jown.alloc(jbytes);
-            MGRT_HIP(hipMemcpy(Jown.p, J, jbytes, hipMemcpyHostToDevice));
+            MGRT_HIP(copy_blocking(Jown.p, J, jbytes, hipMemcpyHostToDevice));
             Jd = Jown.p;
         }
         DevBuf dcoef = upload(coef, c.stream);
@@ -226,7 +226,7 @@ extern "C" int mgrt_project_rows(mgrt_ctx *ctx, int64_t n_traces, int32_t n_samp
         c.timing.call_ms = ms;
         c.timing.step_ms_total = 0;
         std::vector<double> h((size_t)n_traces * npi * M);
-        MGRT_HIP(hipMemcpy(h.data(), dP.p, h.size() * 8, hipMemcpyDeviceToHost));
+        MGRT_HIP(copy_blocking(h.data(), dP.p, h.size() * 8, hipMemcpyDeviceToHost));
         for (int64_t i = 0; i < n_traces; ++i)
             for (int j = 0; j < n_proj; ++j)
                 std::copy(h.begin() + (i * npi + j) * M, h.begin() + (i * npi + j + 1) * M,

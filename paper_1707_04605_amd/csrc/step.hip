@@ -89,7 +89,7 @@ static void fill_values(Ctx &c, StepOp &op) {
     std::vector<T> beta(n);
     op.gamma.resize(n);
     std::vector<int64_t> sptr(op.n_tiles + 1);
-    MGRT_HIP(hipMemcpy(sptr.data(), op.slice_ptr.p, sptr.size() * sizeof(int64_t), hipMemcpyDeviceToHost));
+    MGRT_HIP(copy_blocking(sptr.data(), op.slice_ptr.p, sptr.size() * sizeof(int64_t), hipMemcpyDeviceToHost));
     std::vector<T> vals(sptr[op.n_tiles], T(0));
     parallel_for(op.n_tiles, [&](int64_t t0, int64_t t1) {
         for (int64_t t = t0; t < t1; ++t) {
@@ -689,22 +689,13 @@ void run_batch_t(Ctx &c, StepOp &op, BatchRun &run) {
     if (!run.arena && !(run.flags & MGRT_F_NO_GRAPH) && G % 2 == 0 && run.n_steps >= 2 * G) {
         DevBuf dbase(sizeof(int64_t));
         int64_t *base = dbase.as<int64_t>();
-        hipGraph_t graph = nullptr;
-        if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) == hipSuccess) {
-            try {
-                for (int64_t j = 0; j < G; ++j) issue(j, j, base, hist_chunk != 0 && j == G - 1);
-                hipLaunchKernelGGL(k_step_base, dim3(1), dim3(64), 0, s, base, G, 1);
-            } catch (...) {
-                hipGraph_t g2 = nullptr;
-                (void)hipStreamEndCapture(s, &g2);
-                if (g2) (void)hipGraphDestroy(g2);
-                throw;
-            }
-            MGRT_HIP(hipStreamEndCapture(s, &graph));
-            hipGraphExec_t exec = nullptr;
-            const hipError_t ie = hipGraphInstantiateWithFlags(&exec, graph, 0);
-            (void)hipGraphDestroy(graph);
-            MGRT_HIP(ie);
+        const hipGraphExec_t exec = capture_launches(c, [&](hipStream_t cs) {
+            s = cs;
+            for (int64_t j = 0; j < G; ++j) issue(j, j, base, hist_chunk != 0 && j == G - 1);
+            hipLaunchKernelGGL(k_step_base, dim3(1), dim3(64), 0, s, base, G, 1);
+            s = c.stream;
+        });
+        if (exec) {
             const int64_t nrep = run.n_steps / G;
             hipLaunchKernelGGL(k_step_base, dim3(1), dim3(64), 0, s, base, (int64_t)0, 0);
             if (timing) MGRT_HIP(hipEventRecord(ev[0], s));
@@ -722,8 +713,6 @@ void run_batch_t(Ctx &c, StepOp &op, BatchRun &run) {
                 MGRT_HIP(hipEventElapsedTime(&ms, ev[0], ev[1]));
                 c.timing.step_ms_total += ms;
             }
-        } else {
-            (void)hipGetLastError();
         }
     }
     for (int64_t l = l0; l < run.n_steps; ++l) {
@@ -824,6 +813,37 @@ int64_t pml_entries(const Ctx &c) {
     int64_t ne = 0;
     for (double z : c.pml_zeta) ne += z > 0;
     return ne;
+}
+
+// A stream whose capture was invalidated (by a blocking call of another library in another thread)
+// stays unusable, so captures have a stream of their own, made anew after that.
+hipGraphExec_t capture_launches(Ctx &c, const std::function<void(hipStream_t)> &launches) {
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+    bool ok = false;
+    {
+        std::unique_lock<std::shared_mutex> lk(capture_mutex());
+        if (!c.capture_stream && hipStreamCreateWithFlags(&c.capture_stream, hipStreamNonBlocking) != hipSuccess)
+            c.capture_stream = nullptr;
+        if (c.capture_stream && hipStreamBeginCapture(c.capture_stream, hipStreamCaptureModeThreadLocal) == hipSuccess) {
+            try {
+                launches(c.capture_stream);
+            } catch (...) {
+                (void)hipStreamEndCapture(c.capture_stream, &graph);
+                if (graph) (void)hipGraphDestroy(graph);
+                throw;
+            }
+            ok = hipStreamEndCapture(c.capture_stream, &graph) == hipSuccess && graph;
+        }
+        if (!ok && c.capture_stream) {
+            (void)hipStreamDestroy(c.capture_stream);
+            c.capture_stream = nullptr;
+        }
+    }
+    if (ok && hipGraphInstantiateWithFlags(&exec, graph, 0) != hipSuccess) exec = nullptr;
+    if (graph) (void)hipGraphDestroy(graph);
+    if (!exec) (void)hipGetLastError();
+    return exec;
 }
 
 void hist_flush(const BatchRun &run, int prec, const void *stage, const void *stage2, int64_t nser, int64_t count,

@@ -1313,7 +1313,7 @@ struct TvSystem {
     int solve(const double *b, double *z, const std::vector<double> &gamma, double rtol, int maxit) {
         MGRT_REQUIRE((int64_t)gamma.size() == D.nrows, MGRT_E_ARG, "weights size mismatch");
         if (D.nrows)
-            MGRT_HIP(hipMemcpy(gam.p, gamma.data(), D.nrows * 8, hipMemcpyHostToDevice));
+            MGRT_HIP(copy_blocking(gam.p, gamma.data(), D.nrows * 8, hipMemcpyHostToDevice));
         std::vector<double> hp(M), lam(M);
         bool lam_pos = alpha > 0;
         for (int64_t j = 0; j < M; ++j) {
@@ -1324,7 +1324,7 @@ struct TvSystem {
             lam[j] = alpha * dd;
             lam_pos = lam_pos && lam[j] > 0 && std::isfinite(lam[j]);
         }
-        MGRT_HIP(hipMemcpy(pinv.p, hp.data(), M * 8, hipMemcpyHostToDevice));
+        MGRT_HIP(copy_blocking(pinv.p, hp.data(), M * 8, hipMemcpyHostToDevice));
         lowrank = rows <= LOWRANK_MAX_ROWS && rows < M && lam_pos && build_lowrank(lam);
         const double bnorm = std::sqrt(dot(b, b));
         apply(z, q.as<double>());
@@ -1391,7 +1391,7 @@ const void *device_matrix(Ctx &c, const void *L, int on_device, int64_t rows, in
                           DevBuf &own) {
     if (on_device) return L;
     own.alloc((size_t)rows * M * esz);
-    MGRT_HIP(hipMemcpy(own.p, L, (size_t)rows * M * esz, hipMemcpyHostToDevice));
+    MGRT_HIP(copy_blocking(own.p, L, (size_t)rows * M * esz, hipMemcpyHostToDevice));
     (void)c;
     return own.p;
 }

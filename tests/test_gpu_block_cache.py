@@ -82,11 +82,11 @@ def test_two_threads_share_blocks(mgrt, work):
     a, b = mgrt.context_for_problem(p), mgrt.context_for_problem(q)
 
     def gradients():
-        return [a.misfit_gradient(*args, precision=32) for _ in range(3)]
+        return [a.misfit_gradient(*args, precision=32) for _ in range(8)]
 
     def forwards():
         return [b.forward_traces(q.src, q.rec, q.wavelet, q.dt, q.n_steps, precision=prec)
-                for prec in (32, 64, 32, 64)]
+                for prec in (32, 64) * 5]
 
     ref = gradients(), forwards()
     got = [None, None]
