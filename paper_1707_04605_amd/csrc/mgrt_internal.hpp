@@ -346,13 +346,6 @@ struct Ctx {
     int64_t grid_nx = -1;              // row length of a lexicographic 2D grid, 0: none, -1: not looked at
     std::shared_ptr<void> fft_plans;   // deconv.hip: FFT plans kept per (length, batch, precision)
     mgrt_timing timing{};
-    hipStream_t capture_stream = nullptr;   // runs of steps are captured here, never run (capture_launches)
-    Ctx() = default;
-    Ctx(const Ctx &) = delete;
-    Ctx &operator=(const Ctx &) = delete;
-    ~Ctx() {
-        if (capture_stream) (void)hipStreamDestroy(capture_stream);
-    }
 };
 
 // mesh_ops.hip

@@ -816,28 +816,30 @@ int64_t pml_entries(const Ctx &c) {
 }
 
 // A stream whose capture was invalidated (by a blocking call of another library in another thread)
-// stays unusable, so captures have a stream of their own, made anew after that.
+// stays unusable, so captures have a stream of their own per device, on which nothing runs: one
+// capture is open at a time.  It is made anew after that.
 hipGraphExec_t capture_launches(Ctx &c, const std::function<void(hipStream_t)> &launches) {
+    static auto *streams = new std::map<int, hipStream_t>;     // never destroyed: the runtime may go first
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     bool ok = false;
     {
         std::unique_lock<std::shared_mutex> lk(capture_mutex());
-        if (!c.capture_stream && hipStreamCreateWithFlags(&c.capture_stream, hipStreamNonBlocking) != hipSuccess)
-            c.capture_stream = nullptr;
-        if (c.capture_stream && hipStreamBeginCapture(c.capture_stream, hipStreamCaptureModeThreadLocal) == hipSuccess) {
+        hipStream_t &s = (*streams)[c.device];
+        if (!s && hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) s = nullptr;
+        if (s && hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) == hipSuccess) {
             try {
-                launches(c.capture_stream);
+                launches(s);
             } catch (...) {
-                (void)hipStreamEndCapture(c.capture_stream, &graph);
+                (void)hipStreamEndCapture(s, &graph);
                 if (graph) (void)hipGraphDestroy(graph);
                 throw;
             }
-            ok = hipStreamEndCapture(c.capture_stream, &graph) == hipSuccess && graph;
+            ok = hipStreamEndCapture(s, &graph) == hipSuccess && graph;
         }
-        if (!ok && c.capture_stream) {
-            (void)hipStreamDestroy(c.capture_stream);
-            c.capture_stream = nullptr;
+        if (!ok && s) {
+            (void)hipStreamDestroy(s);
+            s = nullptr;
         }
     }
     if (ok && hipGraphInstantiateWithFlags(&exec, graph, 0) != hipSuccess) exec = nullptr;
