@@ -95,10 +95,10 @@ def tuning(ctx):
 def roofline(tm, n, esz, launches_ms, launches, counter_file=None, tune=None, strips=None):
     """Stepping-kernel roofline: the library's algorithmic bytes of the last call's launches
     (which include velocity and accumulator traffic of adjoint sweeps) over the event-timed
-    launch duration.  Launches of several steps move far fewer bytes per step than HBM could:
-    where the committed counters hold their VALU instructions, those over the duration are the
-    achieved rate and the HBM figures stand beside it; elsewhere the chain of sub-steps
-    bounds them and the HBM fraction only says how little of it is used."""
+    launch duration.  Launches of several steps: where the committed counters hold their VALU
+    instructions and HBM traffic, whichever is nearer its peak is the bound and the other
+    stands beside it; elsewhere the chain of sub-steps bounds them ("latency") and the HBM
+    fraction only says how little of it is used."""
     B, k = tm["batch"], max(1, tm["steps_per_launch"])
     prec = "FP32" if esz == 4 else "FP64"
     nnz_off = int(round(tm["ell_mean_width"] * n))
@@ -134,8 +134,13 @@ def roofline(tm, n, esz, launches_ms, launches, counter_file=None, tune=None, st
     rf["traffic"] = hbm["traffic"]
     if valu:
         rate = valu / avg_launch_s / 1e9
-        rf.update(bound="valu", achieved=rate, peak=VALU_PEAK_GINST, unit="1e9 wave instructions/s",
-                  frac=rate / VALU_PEAK_GINST, valu_instructions_per_launch=valu, hbm=hbm)
+        alu = {"achieved": rate, "peak": VALU_PEAK_GINST, "unit": "1e9 wave instructions/s",
+               "frac": rate / VALU_PEAK_GINST}
+        rf["valu_instructions_per_launch"] = valu
+        if alu["frac"] >= hbm["traffic"] / avg_launch_s / 1e9 / HBM_PEAK_GBS:
+            rf.update(bound="valu", **alu, hbm=hbm)
+        else:
+            rf.update(bound="hbm", valu=alu)
     return rf
 
 
